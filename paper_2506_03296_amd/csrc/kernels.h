@@ -7,8 +7,9 @@
 // group
 //   1. reads context_lens once and derives the partition of plan_policy.h on
 //      its own (block sums, a prefix scan, the longest request for the tight
-//      block-table stride; 32-bit arithmetic unless the batch is too large
-//      for it), so no planner kernel runs before it;
+//      block-table stride; in every wave's registers for up to 256 requests,
+//      by the group through LDS for more; 32-bit arithmetic unless the batch
+//      is too large for it), so no planner kernel runs before it;
 //   2. walks its contiguous range of (request b, kv-head g, block) units
 //      (ranges of equal cost, a pair's cost being its blocks plus a fixed
 //      start-up charge) segment by segment.  In a segment the four waves
@@ -38,6 +39,8 @@
 
 #include <hip/hip_runtime.h>
 #include <stdint.h>
+
+#include <type_traits>
 
 #include "plan_policy.h"
 
@@ -164,6 +167,12 @@ __device__ inline int wave_incl_max(int x)
     x = max(x, __builtin_amdgcn_update_dpp(0, x, 0x142, 0xa, 0xf, false));
     x = max(x, __builtin_amdgcn_update_dpp(0, x, 0x143, 0xc, 0xf, false));
     return x;
+}
+
+// The value of one lane (the same lane index in every lane) as a scalar.
+__device__ inline int lane_value(int x, int lane)
+{
+    return __builtin_amdgcn_readlane(x, lane);
 }
 
 // Max / sum of the values a lane's column holds in the four 16-lane rows of
@@ -384,6 +393,32 @@ __device__ inline NewTokenElems load_new_token_elems(const AttnParams& p, const 
     return e;
 }
 
+// Issues the loads of a segment's blocks 0 and 1 (tile 0 first) and of the ids
+// that follow them, for a segment that the pipeline does not run on into.
+template <bool kCheck>
+__device__ inline void load_first_tiles(const AttnParams& p, const WaveSeg& cs, const int32_t* safe, WaveTiles& st,
+                                        int lane)
+{
+    const int n = cs.n;
+    const uint32_t step = (uint32_t)((size_t)p.Hkv * kBlockSize * kHeadDim);
+    const int koff = k_lane_offset(lane), voff = v_lane_offset(lane);
+    auto id_at = [&](int pos) -> int {
+        const int32_t* a = pos < n ? cs.bt + kWaves * pos : safe;
+        return *(const __attribute__((address_space(4))) int32_t*)a;
+    };
+    auto id_ok = [&](int id) -> bool { return !kCheck || (id >= 0 && (int64_t)id < p.num_blocks); };
+    st.cur0 = id_at(0);
+    st.cur1 = id_at(1);
+    st.nid0 = id_at(2);
+    st.nid1 = id_at(3);
+    const int nb0 = n > 0 && id_ok(st.cur0) ? kSlabBytes : 0;
+    const int nb1 = n > 1 && id_ok(st.cur1) ? kSlabBytes : 0;
+    load_slab(st.kt0, cs.kpair + (uint64_t)(uint32_t)st.cur0 * step, nb0, koff, 64);
+    load_slab(st.vt0, cs.vpair + (uint64_t)(uint32_t)st.cur0 * step, nb0, voff, 256);
+    load_slab(st.kt1, cs.kpair + (uint64_t)(uint32_t)st.cur1 * step, nb1, koff, 64);
+    load_slab(st.vt1, cs.vpair + (uint64_t)(uint32_t)st.cur1 * step, nb1, voff, 256);
+}
+
 // Per-wave attention over its blocks of segment cs; ns is the work group's
 // next segment (n = 0 if none), `safe` any readable block-table entry, pf_next
 // whether the tiles continue into ns, cur_row the block-table row of cs's
@@ -425,19 +460,6 @@ __device__ inline void wave_attend(const AttnParams& p, const WaveSeg& cs, const
     // both segments are long)
     const bool pf = pf_next;
 
-    if (!st.prefetched) {
-        // load the segment's blocks 0 and 1 (tile 0 first)
-        st.cur0 = id_at(true, 0, n > 0);
-        st.cur1 = id_at(true, 1, n > 1);
-        const int nb0 = n > 0 && id_ok(st.cur0) ? kSlabBytes : 0;
-        const int nb1 = n > 1 && id_ok(st.cur1) ? kSlabBytes : 0;
-        load_slab(st.kt0, cs.kpair + (uint64_t)(uint32_t)st.cur0 * step, nb0, koff, 64);
-        load_slab(st.vt0, cs.vpair + (uint64_t)(uint32_t)st.cur0 * step, nb0, voff, 256);
-        load_slab(st.kt1, cs.kpair + (uint64_t)(uint32_t)st.cur1 * step, nb1, koff, 64);
-        load_slab(st.vt1, cs.vpair + (uint64_t)(uint32_t)st.cur1 * step, nb1, voff, 256);
-        st.nid0 = id_at(true, 2, n > 2);
-        st.nid1 = id_at(true, 3, n > 3);
-    }
     // Everything loaded before the loop (the tiles, mostly issued during the
     // previous segment's last steps, and this segment's Q^T, issued one
     // segment ahead) is complete from here on, so the loop's own waits are
@@ -655,7 +677,6 @@ __global__ __launch_bounds__(kAttnThreads) __attribute__((amdgpu_waves_per_eu(2)
     __shared__ int s_wmax[kWaves];
     __shared__ int s_wcnt[kWaves];
     __shared__ int s_loc_b;
-    __shared__ int64_t s_loc_pre;
     __shared__ int s_loc_g;
     __shared__ int s_loc_blk;
     __shared__ int64_t s_loc_vf;
@@ -672,13 +693,8 @@ __global__ __launch_bounds__(kAttnThreads) __attribute__((amdgpu_waves_per_eu(2)
     if (tid < kTraceWords) s_trace[tid] = tid == 0 ? trace_clock() : 0;
 #endif
 
-    // 1. partition.  context_lens is read from memory once: each thread sums
-    // the blocks of a contiguous run of requests (and keeps the lengths in
-    // LDS when they fit); wave-level scans plus one barrier give the prefix
-    // sums, the total, the longest request and the non-empty requests.
-    const int seg = (B + kAttnThreads - 1) / kAttnThreads;
-    const int r0 = min(B, tid * seg);
-    const int r1 = min(B, r0 + seg);
+    // 1. partition (positions on the cost line of plan_policy.h: every
+    // non-empty pair's K cost positions, then its blocks)
     // with the input check, a context longer than an explicit table row is
     // cut to the row (and reported)
     const int64_t row_tokens = p.bt_stride * kBlockSize;
@@ -694,6 +710,101 @@ __global__ __launch_bounds__(kAttnThreads) __attribute__((amdgpu_waves_per_eu(2)
         if (is_cut(L)) return (int)row_tokens;
         return append && L > 0 ? L - 1 : L;
     };
+    auto len_of = [&](int b) -> int { return cached ? s_lens[b] : cached_len(lens[b]); };
+    const int K = p.seg_cost;
+    int64_t V = 0, W = 0, v0 = 0, v1 = 0, vf = 0, stride = p.bt_stride;
+    int b = 0, g = 0, blk = 0, L = 0;
+    bool all_nonempty = false;
+
+    // The prologue is serial code of every work group: no K/V byte is asked
+    // for before its end, and a wave issues one instruction in four cycles at
+    // best, so its time is its instruction count.  For a batch of up to
+    // kLanes * R requests every wave derives the partition on its own, lane i
+    // holding R consecutive requests (R = 1 up to 64 requests, else 4): one
+    // scan of the requests' cost, ballots and lane reads, no barrier and no
+    // LDS round trip, all results in scalar registers, products in 32 bits.
+    // Returns false, with nothing decided, when 32 bits do not hold them
+    // (plan bound: V (launched + 1) < 2^32).  Against the group-wide form
+    // below, a work group's time from its start to its first segment falls
+    // from 1.9 to 1.1 us for 16 requests and from 1.7 to 1.0 us for 4.
+    auto plan_in_wave = [&](auto runs) -> bool {
+        constexpr int R = decltype(runs)::value;
+        const int run = R == 1 ? 1 : (B + 63) >> 6;
+        int Ls[R], nbs[R];
+        unsigned cost = 0;
+        int maxb = 0, nonempty = 0;
+#pragma unroll
+        for (int i = 0; i < R; ++i) {
+            const int r = lane * run + i;
+            const bool in = i < run && r < B;
+            const int raw = in ? lens[r] : 0;
+            if (in && is_cut(raw)) report_error(p, kErrTableRow);
+            Ls[i] = cached_len(raw);
+            nbs[i] = (int)blocks_of(Ls[i], kBlockSize);
+            maxb = max(maxb, (int)blocks_of(is_cut(raw) ? (int)row_tokens : raw, kBlockSize));
+            nonempty += __popcll(__ballot(nbs[i] > 0));
+            cost += nbs[i] > 0 ? (unsigned)(nbs[i] + K) : 0u;
+            if (in) s_lens[r] = Ls[i];
+        }
+        const unsigned hi = (unsigned)wave_incl_sum((int)cost), lo = hi - cost;
+        const unsigned total = (unsigned)lane_value((int)hi, 63);
+        if (stride == 0) stride = lane_value(wave_incl_max(maxb), 63);
+        nonempty = uniform(nonempty);
+        all_nonempty = nonempty == B;
+        const uint64_t V64 = (uint64_t)total * (unsigned)p.Hkv;
+        if ((V64 >> 32) != 0 || V64 * ((unsigned)p.launched + 1ull) > 0xffffffffull) return false;
+        const unsigned hk = (unsigned)p.Hkv, V32 = (unsigned)V64;
+        const unsigned units = V32 - (unsigned)K * (unsigned)nonempty * hk;
+        const unsigned W32 = clamp_workers<uint32_t>(units >> __builtin_ctz((unsigned)p.min_units), units,
+                                                     (uint32_t)p.launched, (uint32_t)nonempty * hk, (uint32_t)p.cus);
+        V = V32;
+        W = W32;
+        if (units == 0 || (unsigned)w >= W32) return true;
+        const unsigned ends = ((unsigned)w + (lane & 1)) * V32 / W32;   // lane 0: start, lane 1: end
+        const unsigned u0 = (unsigned)lane_value((int)ends, 0);
+        v0 = u0;
+        v1 = (unsigned)lane_value((int)ends, 1);
+        // the lane whose requests hold u0, the request, the pair
+        const int ln = __builtin_ctzll(__ballot(lo * hk <= u0 && u0 < hi * hk));
+        unsigned vpre = (unsigned)lane_value((int)lo, ln) * hk;
+        int nb = lane_value(nbs[0], ln);
+        L = lane_value(Ls[0], ln);
+        b = ln * run;
+#pragma unroll
+        for (int i = 1; i < R; ++i) {
+            const unsigned span = nb > 0 ? (unsigned)(nb + K) * hk : 0u;
+            if (u0 >= vpre + span) {
+                vpre += span;
+                nb = lane_value(nbs[i], ln);
+                L = lane_value(Ls[i], ln);
+                ++b;
+            }
+        }
+        const unsigned per = (unsigned)(nb + K);
+        // kv-head: pair g of the request starts at vpre + g per
+        g = hk <= 64 ? __popcll(__ballot((unsigned)lane < hk && vpre + (unsigned)lane * per <= u0)) - 1
+                     : uniform((int)((u0 - vpre) / per));
+        const unsigned first = vpre + (unsigned)g * per + (unsigned)K;   // position of the pair's block 0
+        vf = first;
+        blk = u0 > first ? (int)(u0 - first) : 0;
+        return true;
+    };
+    bool planned = false;
+    if (B <= 64)
+        planned = plan_in_wave(std::integral_constant<int, 1>());
+    else if (B <= 256)
+        planned = plan_in_wave(std::integral_constant<int, 4>());
+
+    // Larger batches (and partitions past 32 bits): context_lens is read once
+    // by the group, each thread sums the blocks of a contiguous run of
+    // requests (and keeps the lengths in LDS when they fit); wave-level scans
+    // plus one barrier give the prefix sums, the total, the longest request
+    // and the non-empty requests.  Redundant per-wave runs of more than four
+    // requests would cost more than the barriers they save.
+    if (!planned) {
+    const int seg = (B + kAttnThreads - 1) / kAttnThreads;
+    const int r0 = min(B, tid * seg);
+    const int r1 = min(B, r0 + seg);
     int tsum = 0, tmax = 0, tcnt = 0;
     for (int b = r0; b < r1; ++b) {
         const int raw = lens[b];
@@ -726,22 +837,15 @@ __global__ __launch_bounds__(kAttnThreads) __attribute__((amdgpu_waves_per_eu(2)
         maxb = max(maxb, s_wmax[v]);
         nonempty += s_wcnt[v];
     }
-    auto len_of = [&](int b) -> int { return cached ? s_lens[b] : cached_len(lens[b]); };
-
     const int64_t units = (int64_t)uniform(total) * p.Hkv;
     const int64_t pairs = (int64_t)uniform(nonempty) * p.Hkv;
-    const int64_t stride = p.bt_stride > 0 ? p.bt_stride : (int64_t)uniform(maxb);
-    // the cost line: every non-empty pair's K cost positions, then its blocks
-    const int64_t K = p.seg_cost;
-    const int64_t V = units + K * pairs;
-    // The prologue is serial code of one wave per work group, so its time is
-    // its instruction count: when V (launched + 1) < 2^32 (any batch below
-    // about 8 M units at the default grid) every product below fits 32 bits
-    // and the partition runs in 32-bit arithmetic, else in 64-bit; both give
-    // the same ranges.  Lanes 0 and 1 find the range's two ends in one
-    // division.
+    stride = p.bt_stride > 0 ? p.bt_stride : (int64_t)uniform(maxb);
+    V = units + (int64_t)K * pairs;
+    // When V (launched + 1) < 2^32 (any batch below about 8 M units at the
+    // default grid) every product below fits 32 bits and the partition runs in
+    // 32-bit arithmetic, else in 64-bit; both give the same ranges.  Lanes 0
+    // and 1 find the range's two ends in one division.
     const bool narrow = ((uint64_t)V >> 32) == 0 && (uint64_t)V * ((uint64_t)p.launched + 1) <= 0xffffffffull;
-    int64_t W, v0, v1;
     if (narrow) {
         const uint32_t W32 = active_workers_t<uint32_t>((uint32_t)units, (uint32_t)p.launched, (uint32_t)p.min_units,
                                                         (uint32_t)pairs, (uint32_t)p.cus);
@@ -771,7 +875,7 @@ __global__ __launch_bounds__(kAttnThreads) __attribute__((amdgpu_waves_per_eu(2)
         const I lo = (I)(incl - tsum) + Kc * (I)(incl_cnt - own_cnt);
         const I hi = (I)incl + Kc * (I)incl_cnt;
         if (lo * hk <= at && at < hi * hk) {
-            I pre = (I)(incl - tsum), vpre = lo * hk;
+            I vpre = lo * hk;
             for (int b = r0; b < r1; ++b) {
                 // with one request per thread, its block count is the scan's
                 const I nb = seg == 1 ? (I)tsum : (I)blocks_of(len_of(b), kBlockSize);
@@ -781,13 +885,11 @@ __global__ __launch_bounds__(kAttnThreads) __attribute__((amdgpu_waves_per_eu(2)
                     const I g = div_floor(at - vpre, nb + Kc);
                     const I vf = vpre + g * (nb + Kc) + Kc;   // position of the pair's block 0
                     s_loc_b = b;
-                    s_loc_pre = (int64_t)pre;
                     s_loc_g = (int)g;
                     s_loc_blk = (int)(at > vf ? at - vf : 0);
                     s_loc_vf = (int64_t)vf;
                     break;
                 }
-                pre += nb;
                 vpre += span;
             }
         }
@@ -800,6 +902,16 @@ __global__ __launch_bounds__(kAttnThreads) __attribute__((amdgpu_waves_per_eu(2)
     }
     __syncthreads();
 
+    if (v0 < v1) {
+        b = uniform(s_loc_b);
+        g = uniform(s_loc_g);
+        blk = uniform(s_loc_blk);
+        vf = uniform64(s_loc_vf);
+        L = uniform(len_of(b));
+    }
+    all_nonempty = uniform(nonempty) == B;
+    }
+
     // A segment is the worker's blocks of one pair: from block blk of the pair
     // whose block 0 lies at position vf, up to the pair's end or the worker's
     // range end v1, whichever comes first (none when v1 falls on or before
@@ -808,15 +920,8 @@ __global__ __launch_bounds__(kAttnThreads) __attribute__((amdgpu_waves_per_eu(2)
         const int64_t left = v1 - (vf_ + blk_);
         return left <= 0 ? 0 : (int)min((int64_t)(nb_ - blk_), left);
     };
-    int b = 0, g = 0, blk = 0, L = 0, nb = 0, take = 0;
-    int64_t pre = 0, vf = 0;
+    int nb = 0, take = 0;
     if (v0 < v1) {
-        b = uniform(s_loc_b);
-        pre = uniform64(s_loc_pre);
-        g = uniform(s_loc_g);
-        blk = uniform(s_loc_blk);
-        vf = uniform64(s_loc_vf);
-        L = uniform(len_of(b));
         nb = (int)blocks_of(L, kBlockSize);
         take = seg_take(nb, blk, vf);
     }
@@ -824,8 +929,7 @@ __global__ __launch_bounds__(kAttnThreads) __attribute__((amdgpu_waves_per_eu(2)
     if (take > 0) {
     // Moves a segment cursor past its segment to the worker's next one;
     // false when the worker's range is done.
-    auto advance = [&](int& b_, int64_t& pre_, int& L_, int& nb_, int& g_, int& blk_, int64_t& vf_,
-                       int take_) -> bool {
+    auto advance = [&](int& b_, int& L_, int& nb_, int& g_, int& blk_, int64_t& vf_, int take_) -> bool {
         blk_ += take_;
         if (blk_ < nb_) return false;   // the range ended inside the pair
         const int64_t vnext = vf_ + nb_ + K;   // the next pair's block 0
@@ -834,7 +938,6 @@ __global__ __launch_bounds__(kAttnThreads) __attribute__((amdgpu_waves_per_eu(2)
         vf_ = vnext;
         if (++g_ == p.Hkv) {
             g_ = 0;
-            pre_ += nb_;
             do {
                 ++b_;
             } while (b_ < B && len_of(b_) <= 0);
@@ -857,14 +960,21 @@ __global__ __launch_bounds__(kAttnThreads) __attribute__((amdgpu_waves_per_eu(2)
     load_q<G>(st.qnext, cs, lane);
     while (true) {
         int b2 = b, L2 = L, nb2 = nb, g2 = g, blk2 = blk;
-        int64_t pre2 = pre, vf2 = vf;
-        const bool more = advance(b2, pre2, L2, nb2, g2, blk2, vf2, take);
+        int64_t vf2 = vf;
+        // the loads of a segment that the pipeline did not run on into go out
+        // before the next segment is looked up
+        if (!st.prefetched) load_first_tiles<kCheck>(p, cs, bt, st, lane);
+        const bool more = advance(b2, L2, nb2, g2, blk2, vf2, take);
         const int take2 = more ? seg_take(nb2, blk2, vf2) : 0;
         WaveSeg ns = cs;
         ns.n = 0;
         if (more)
             ns = wave_seg<G>(p, bt + (size_t)uniform(b2) * (size_t)stride, b2, g2, blk2, blk2 + take2, wave,
                              lane);
+        // the pair's first and last work groups: this one, unless the range
+        // cuts the pair (found here, while the loads are in flight)
+        const int64_t wf = blk == 0 ? w : (int64_t)uniform((int)worker_of(vf, V, W));
+        const int64_t wl = blk + take == nb ? w : (int64_t)uniform((int)worker_of(vf + nb - 1, V, W));
         NewTokenElems ne;
         wave_attend<G, kCheck, kAppend>(p, cs, ns, bt,
                                         more && take >= kPrefetchBlocks && take2 >= kPrefetchBlocks, L,
@@ -879,8 +989,6 @@ __global__ __launch_bounds__(kAttnThreads) __attribute__((amdgpu_waves_per_eu(2)
 #endif
 
         // 3. merge the waves, emit rows or a partial
-        const int64_t wf = worker_of(vf, V, W);
-        const int64_t wl = worker_of(vf + nb - 1, V, W);
         const int64_t slot = partial_slot(w, wf);
         for (int idx = tid; idx < G * D; idx += kAttnThreads) {
             const int h = idx / D, dim = idx % D;
@@ -979,7 +1087,6 @@ __global__ __launch_bounds__(kAttnThreads) __attribute__((amdgpu_waves_per_eu(2)
 
         if (!more) break;
         b = b2;
-        pre = pre2;
         vf = vf2;
         L = L2;
         nb = nb2;
@@ -993,7 +1100,7 @@ __global__ __launch_bounds__(kAttnThreads) __attribute__((amdgpu_waves_per_eu(2)
     // rows of empty requests are zeros (and lse = -inf); with the fused
     // append a request whose only token is the current one returns its V row
     // (lse = its scaled logit) and stores its K/V
-    for (int b = (int)w; b < B; b += (int)gridDim.x) {
+    for (int b = all_nonempty ? B : (int)w; b < B; b += (int)gridDim.x) {
         if (len_of(b) > 0) continue;
         if (append && lens[b] == 1) {
             const size_t nrow = (size_t)b * p.new_stride;

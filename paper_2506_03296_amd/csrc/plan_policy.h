@@ -31,6 +31,7 @@ namespace apex {
 constexpr int kHeadDim = 128;
 constexpr int kBlockSize = 16;
 constexpr int kMinUnitsPerWorker = 16;  // four blocks per wave of a 4-wave work group
+static_assert((kMinUnitsPerWorker & (kMinUnitsPerWorker - 1)) == 0, "the kernel divides by it with a shift");
 constexpr int64_t kUnitsPerCuForOne = 1024;   // 8 MiB of K/V per CU
 // Cost of a pair's segment in units: a short segment takes about 2-3 us of
 // latency (block ids, first tiles, merge, emit), the time a work group
@@ -72,14 +73,20 @@ __host__ __device__ inline int64_t blocks_of(int32_t len, int bs)
 // second group sharing the CU.
 // The integer type I is int64_t, or uint32_t where the caller has shown that
 // every operand and cus * kUnitsPerCuForOne fit (the kernel's 32-bit path).
+// clamp_workers takes the quotient units / min_units from the caller.
 template <typename I>
-__host__ __device__ inline I active_workers_t(I units, I launched, I min_units, I pairs, I cus)
+__host__ __device__ inline I clamp_workers(I w, I units, I launched, I pairs, I cus)
 {
     if (cus > 0 && pairs <= cus && units <= cus * (I)kUnitsPerCuForOne && launched > cus) launched = cus;
-    I w = div_floor(units, min_units > 0 ? min_units : (I)1);
     if (w < pairs) w = pairs;
     if (w < 1) w = 1;
     return w < launched ? w : launched;
+}
+
+template <typename I>
+__host__ __device__ inline I active_workers_t(I units, I launched, I min_units, I pairs, I cus)
+{
+    return clamp_workers<I>(div_floor(units, min_units > 0 ? min_units : (I)1), units, launched, pairs, cus);
 }
 
 __host__ __device__ inline int64_t active_workers(int64_t units, int64_t launched, int min_units,
