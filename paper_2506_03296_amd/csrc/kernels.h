@@ -48,12 +48,14 @@ namespace apex {
 
 typedef _Float16 f16;
 typedef _Float16 f16x2 __attribute__((ext_vector_type(2)));
+typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 
 constexpr int kAttnThreads = 256;
 constexpr int kWaves = kAttnThreads / 64;
 constexpr int kCachedLens = 2048;   // context_lens kept in LDS up to this batch size
-constexpr int kCombineChunk = 8;    // partials loaded at once by the combining work group
+constexpr int kStageFloats = 2048;  // LDS of one wave: its merged state, or the partials it combines
+constexpr int kFewPartials = 4;     // partials that the emitting threads combine on their own
 
 struct AttnParams {
     const f16* q;          // [B][Hq][D]
@@ -222,11 +224,6 @@ __device__ inline void store_coherent(float* p, float v)
     __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-__device__ inline float load_coherent(const float* p)
-{
-    return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-
 typedef _Float16 f16x4 __attribute__((ext_vector_type(4)));
 typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
@@ -248,6 +245,9 @@ constexpr int kRawBufferWord3 = 0x00020000;
 // Cache policy of the K/V loads: non-temporal (bit 1) -- each row is read
 // exactly once per call, so it should not displace reusable lines.
 constexpr int kStreamingLoad = 2;
+// Cache policy of a wide device-coherent load (sc1), the counterpart of
+// store_coherent.
+constexpr int kCoherentLoad = 16;
 
 // Operand layouts of one slab (lane = 16 q + c, q = lane / 16, c = lane % 16):
 //   K: word i of lane (c, q) = token c, dims [32i + 8q, +8)   (A of S^T = K Q^T)
@@ -362,31 +362,44 @@ __device__ inline void new_token_logits(const AttnParams& p, const NewTokenRows<
     }
 }
 
-// The current token's K and V elements `dim` of kv-head g of request b and
-// the id of the block that holds its slot (position Lc - 1, Lc = the full
-// length), loaded ahead of the emit that needs them.  With the input check a
-// position past an explicit table row (a context cut to its row, already
-// reported) has no slot: the row's last slot holds a cached token.  The
-// slot's table entry is the same for the whole work group, so it is read
+// Elements of a (request, kv-head) pair's G output rows that one thread of the
+// merge and emit owns: consecutive dims of one head, so that the whole work
+// group covers the rows in one pass (G = 1: its first half).  The merge is
+// bound by its instructions: one pass with vector LDS reads takes 0.25-0.3 us
+// where G / 2 passes over single elements took 0.65 (G = 4) and 0.95 (G = 8).
+template <int G>
+constexpr int kEmitElems = G >= 2 ? G * kHeadDim / kAttnThreads : 1;
+
+template <typename T, int N>
+struct vec_of {
+    typedef T type __attribute__((ext_vector_type(N)));
+};
+
+// The current token's K and V elements [dim, dim + N) of kv-head g of request
+// b and the id of the block that holds its slot (position Lc - 1, Lc = the
+// full length), loaded ahead of the emit that needs them.  With the input
+// check a position past an explicit table row (a context cut to its row,
+// already reported) has no slot: the row's last slot holds a cached token.
+// The slot's table entry is the same for the whole work group, so it is read
 // through the constant address space (the scalar path); `safe` is any
-// readable entry, read instead when there is no slot.
-// (The emit's loops give a thread elements idx = tid + k kAttnThreads, all
-// of one dim when kAttnThreads is a multiple of the head dimension.)
-static_assert(kAttnThreads % kHeadDim == 0, "a thread's emit elements share one dim");
+// readable entry, read instead when there is no slot.  (dim is a multiple of
+// N <= 4 and every row starts at a multiple of 8 elements: aligned vectors.)
+template <int N>
 struct NewTokenElems {
-    f16 kn, vn;
+    typename vec_of<f16, N>::type kn, vn;
     int id;
     bool in_row;
 };
 
-template <bool kCheck>
-__device__ inline NewTokenElems load_new_token_elems(const AttnParams& p, const int32_t* bt_row,
-                                                     const int32_t* safe, int b, int g, int Lc, int dim)
+template <bool kCheck, int N>
+__device__ inline NewTokenElems<N> load_new_token_elems(const AttnParams& p, const int32_t* bt_row,
+                                                        const int32_t* safe, int b, int g, int Lc, int dim)
 {
-    NewTokenElems e;
+    typedef typename vec_of<f16, N>::type f16xN;
+    NewTokenElems<N> e;
     const size_t src = (size_t)b * p.new_stride + (size_t)g * kHeadDim + dim;
-    e.kn = p.k_new[src];
-    e.vn = p.v_new[src];
+    e.kn = *(const f16xN*)(p.k_new + src);
+    e.vn = *(const f16xN*)(p.v_new + src);
     e.in_row = !(kCheck && p.bt_stride > 0 && (int64_t)((Lc - 1) / kBlockSize) >= p.bt_stride);
     const int32_t* a = e.in_row ? bt_row + (Lc - 1) / kBlockSize : safe;
     e.id = *(const __attribute__((address_space(4))) int32_t*)a;
@@ -423,7 +436,7 @@ __device__ inline void load_first_tiles(const AttnParams& p, const WaveSeg& cs, 
 // next segment (n = 0 if none), `safe` any readable block-table entry, pf_next
 // whether the tiles continue into ns, cur_row the block-table row of cs's
 // request (with the fused append, ne receives this thread's elements of the
-// current token for the emit: dim = thread index mod 128).  Lane
+// current token for the emit).  Lane
 // (h = lane % 16, q = lane / 16) keeps m (running max of head h, log2 units,
 // equal on the four lanes of h), l (sum of the weights of its tokens) and
 // acc[t][i] (running P.V of head h at dim 32q + 8i + t).  On return the
@@ -433,8 +446,8 @@ template <int G, bool kCheck, bool kAppend>
 __device__ inline void wave_attend(const AttnParams& p, const WaveSeg& cs, const WaveSeg& ns,
                                    const int32_t* safe, bool pf_next, int L, WaveTiles& st, int wave,
                                    int lane,
-                                   float (*s_acc)[G][kHeadDim], float (*s_m)[G], float (*s_l)[G],
-                                   float* s_new, const int32_t* cur_row, NewTokenElems& ne)
+                                   float (*s_acc)[kStageFloats], float (*s_m)[G], float (*s_l)[G],
+                                   float* s_new, const int32_t* cur_row, NewTokenElems<kEmitElems<G>>& ne)
 {
     constexpr int D = kHeadDim;
     constexpr int BS = kBlockSize;
@@ -481,7 +494,8 @@ __device__ inline void wave_attend(const AttnParams& p, const WaveSeg& cs, const
     NewTokenRows<G> nt;
     if (kAppend) {
         load_new_token_rows<G>(p, cs.b, cs.g, lane, nt);
-        ne = load_new_token_elems<kCheck>(p, cur_row, safe, cs.b, cs.g, L + 1, (wave * 64 + lane) % D);
+        ne = load_new_token_elems<kCheck, kEmitElems<G>>(p, cur_row, safe, cs.b, cs.g, L + 1,
+                                                         (wave * 64 + lane) * kEmitElems<G> % D);
     }
 
     float m = -INFINITY, l = 0.f;
@@ -585,7 +599,6 @@ __device__ inline void wave_attend(const AttnParams& p, const WaveSeg& cs, const
         }
         // O^T += V^T P^T, eight 16-dim tiles, the high parts of P, then the
         // low parts (independent accumulators between the two passes)
-        typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
 #pragma unroll
         for (int t = 0; t < 8; ++t) {
             const u32x2 av = {a[t][0], a[t][1]};
@@ -614,7 +627,7 @@ __device__ inline void wave_attend(const AttnParams& p, const WaveSeg& cs, const
     if (col < G) {
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
-            float* dst = &s_acc[wave][col][32 * q + 8 * i];
+            float* dst = &s_acc[wave][col * D + 32 * q + 8 * i];
             *(f32x4*)dst = f32x4{acc[0][i], acc[1][i], acc[2][i], acc[3][i]};
             *(f32x4*)(dst + 4) = f32x4{acc[4][i], acc[5][i], acc[6][i], acc[7][i]};
         }
@@ -625,33 +638,44 @@ __device__ inline void wave_attend(const AttnParams& p, const WaveSeg& cs, const
     }
 }
 
-__device__ inline void write_row(const AttnParams& p, int b, int head, int dim, float M, float num,
-                                 float den)
+// N consecutive dims of one head's merged state: running max M (log2 units;
+// -inf when empty), numerators and denominator relative to it.
+template <int N>
+struct RowState {
+    float M, den;
+    typename vec_of<float, N>::type num;
+};
+
+template <int N>
+__device__ inline void write_row(const AttnParams& p, int b, int head, int dim, const RowState<N>& r)
 {
-    const float o = den > 0.f ? num / den : 0.f;
-    p.out[((size_t)b * p.Hq + head) * kHeadDim + dim] = (f16)o;
+    typename vec_of<f16, N>::type o;
+#pragma unroll
+    for (int i = 0; i < N; ++i) o[i] = (f16)(r.den > 0.f ? r.num[i] / r.den : 0.f);
+    *(typename vec_of<f16, N>::type*)&p.out[((size_t)b * p.Hq + head) * kHeadDim + dim] = o;
     if (p.lse && dim == 0)
         p.lse[(size_t)b * p.Hq + head] =
-            den > 0.f ? (M + __log2f(den)) * 0.69314718055994531f : -INFINITY;
+            r.den > 0.f ? (r.M + __log2f(r.den)) * 0.69314718055994531f : -INFINITY;
 }
 
-// Folds the current token (logit sn in log2 units, value vn) into a merged
-// state: running max M (log2 units; -inf when empty) and num, den relative
-// to it, with its fp32 weight.
-__device__ inline void fold_new_token(float sn, float vn, float& M, float& num, float& den)
+// Folds the current token (logit sn in log2 units, values vn) into a merged
+// state with its fp32 weight.
+template <int N>
+__device__ inline void fold_new_token(float sn, typename vec_of<f16, N>::type vn, RowState<N>& r)
 {
-    const float M2 = fmaxf(M, sn);
-    const float r = M == -INFINITY ? 0.f : exp2_fast(M - M2);
+    const float M2 = fmaxf(r.M, sn);
+    const float f = r.M == -INFINITY ? 0.f : exp2_fast(r.M - M2);
     const float wgt = exp2_fast(sn - M2);
-    num = fmaf(wgt, vn, num * r);
-    den = fmaf(den, r, wgt);
-    M = M2;
+#pragma unroll
+    for (int i = 0; i < N; ++i) r.num[i] = fmaf(wgt, (float)vn[i], r.num[i] * f);
+    r.den = fmaf(r.den, f, wgt);
+    r.M = M2;
 }
 
 // Writes those elements to the slot (with the input check, a block id outside
 // the pool is reported and not written).
-template <bool kCheck>
-__device__ inline void store_new_token(const AttnParams& p, const NewTokenElems& e, int g, int Lc, int dim)
+template <bool kCheck, int N>
+__device__ inline void store_new_token(const AttnParams& p, const NewTokenElems<N>& e, int g, int Lc, int dim)
 {
     if (!e.in_row) return;
     if (kCheck && !(e.id >= 0 && (int64_t)e.id < p.num_blocks)) {
@@ -659,8 +683,178 @@ __device__ inline void store_new_token(const AttnParams& p, const NewTokenElems&
         return;
     }
     const size_t dst = (((size_t)(uint32_t)e.id * p.Hkv + g) * kBlockSize + (Lc - 1) % kBlockSize) * kHeadDim + dim;
-    p.k_store[dst] = e.kn;
-    p.v_store[dst] = e.vn;
+    *(typename vec_of<f16, N>::type*)&p.k_store[dst] = e.kn;
+    *(typename vec_of<f16, N>::type*)&p.v_store[dst] = e.vn;
+}
+
+// The four waves' states of head h (s_acc, s_m, s_l) at dims [dim, dim + N),
+// merged.
+template <int G, int N>
+__device__ inline RowState<N> merge_waves(const float (*s_acc)[kStageFloats], const float (*s_m)[G],
+                                          const float (*s_l)[G], int h, int dim)
+{
+    typedef typename vec_of<float, N>::type f32xN;
+    RowState<N> r;
+    r.M = s_m[0][h];
+#pragma unroll
+    for (int q = 1; q < kWaves; ++q) r.M = fmaxf(r.M, s_m[q][h]);
+    const float Ms = r.M == -INFINITY ? 0.f : r.M;
+    r.den = 0.f;
+    r.num = 0.f;
+#pragma unroll
+    for (int q = 0; q < kWaves; ++q) {
+        const float f = exp2_fast(s_m[q][h] - Ms);
+        const f32xN a = *(const f32xN*)&s_acc[q][h * kHeadDim + dim];
+        r.den = fmaf(f, s_l[q][h], r.den);
+#pragma unroll
+        for (int i = 0; i < N; ++i) r.num[i] = fmaf(f, a[i], r.num[i]);
+    }
+    return r;
+}
+
+// The partials of a split pair: contributor c (work group wf + c) left its
+// accumulators and (max, sum) pairs in slot 2 (wf + c), the first one in slot
+// 2 wf + 1 (partial_slot).  Resources over up to n contributors from c0 on;
+// offsets past them read zeros.
+template <int G>
+struct Partials {
+    static constexpr int kRow = G * kHeadDim * 4, kMl = G * 8;   // bytes of a slot in pacc and pml
+    __amdgpu_buffer_rsrc_t acc, ml;
+    int c0;
+    __device__ inline Partials(const AttnParams& p, int wf, int c0_, int n) : c0(c0_)
+    {
+        const int64_t slot = 2 * (int64_t)(wf + c0_);
+        acc = __builtin_amdgcn_make_buffer_rsrc((void*)uniform_ptr(p.pacc + slot * (G * kHeadDim)), (short)0,
+                                                n * 2 * kRow, kRawBufferWord3);
+        ml = __builtin_amdgcn_make_buffer_rsrc((void*)uniform_ptr(p.pml + slot * (G * 2)), (short)0, n * 2 * kMl,
+                                               kRawBufferWord3);
+    }
+    // slot of contributor c0 + j, counted from contributor c0's even slot
+    __device__ inline int slot(int j) const { return 2 * j + (j == 0 && c0 == 0); }
+};
+
+
+// Rescales r to the running max of C more (max, sum) pairs and adds their
+// sums; cf gets the contributors' factors.
+template <int N, int C>
+__device__ inline void fold_sums(const u32x2 (&ml)[C], int n, RowState<N>& r, float (&cf)[C])
+{
+    float Mn = r.M;
+#pragma unroll
+    for (int j = 0; j < C; ++j) {
+        cf[j] = j < n ? __uint_as_float(ml[j][0]) : -INFINITY;
+        Mn = fmaxf(Mn, cf[j]);
+    }
+    const float Ms = Mn == -INFINITY ? 0.f : Mn;
+    const float f0 = exp2_fast(r.M - Ms);
+    r.den *= f0;
+    r.num *= f0;
+    r.M = Mn;
+#pragma unroll
+    for (int j = 0; j < C; ++j) {
+        cf[j] = exp2_fast(cf[j] - Ms);
+        r.den = fmaf(cf[j], __uint_as_float(ml[j][1]), r.den);
+    }
+}
+
+// Combines up to C partials of a pair at elements [e0, e0 + N) of its rows
+// (all of head h), all in flight at once.  Up to kFewPartials this is faster
+// than combine_wave, which ends in another LDS merge (4 requests of 1024
+// tokens, 4-5 partials a pair: 9.5 us with the line at 4, 9.8 at 8).
+template <int G, int N, int C>
+__device__ inline void combine_few(const AttnParams& p, int wf, int nc, int e0, int h, RowState<N>& r)
+{
+    typedef typename vec_of<float, N>::type f32xN;
+    const Partials<G> ps(p, wf, 0, nc);
+    u32x2 ml[C];
+    f32xN a[C];
+#pragma unroll
+    for (int j = 0; j < C; ++j) {
+        ml[j] = __builtin_amdgcn_raw_buffer_load_b64(ps.ml, h * 8 + ps.slot(j) * ps.kMl, 0, kCoherentLoad);
+        const int off = e0 * 4 + ps.slot(j) * ps.kRow;
+        if constexpr (N == 1)
+            a[j] = __builtin_bit_cast(f32xN, __builtin_amdgcn_raw_buffer_load_b32(ps.acc, off, 0, kCoherentLoad));
+        else if constexpr (N == 2)
+            a[j] = __builtin_bit_cast(f32xN, __builtin_amdgcn_raw_buffer_load_b64(ps.acc, off, 0, kCoherentLoad));
+        else
+            a[j] = __builtin_bit_cast(f32xN, __builtin_amdgcn_raw_buffer_load_b128(ps.acc, off, 0, kCoherentLoad));
+    }
+    float cf[C];
+    fold_sums<N, C>(ml, nc, r, cf);
+#pragma unroll
+    for (int j = 0; j < C; ++j)
+#pragma unroll
+        for (int i = 0; i < N; ++i) r.num[i] = fmaf(cf[j], a[j][i], r.num[i]);
+}
+
+// 16 bytes per lane from offset `off` of r (device-coherent) straight into LDS
+// at dst + 16 * lane, without passing through registers.
+__device__ inline void load_to_lds(__amdgpu_buffer_rsrc_t r, float* dst, int off)
+{
+#ifdef __HIP_DEVICE_COMPILE__
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (__attribute__((address_space(3))) void*)dst, 16, off, 0, 0,
+                                             kCoherentLoad);
+#endif
+}
+
+// Combines contributors [c0, c1) of a pair into this wave's state in LDS (as
+// wave_attend leaves it).  What bounds a combine is the round trips to the
+// partials (about 0.6 us each) and then the instructions, not bytes: one
+// thread per output element walking all contributors in eights took 4 us for
+// the 32 of a 131072-token pair.  So the four waves share the contributors,
+// every lane owns 2 G consecutive elements, and the rows go straight into the
+// wave's LDS stage (the registers are taken by the tiles).  Kernel time,
+// before -> after: one 131071-token request 87.6 -> 84.5 us, one 4096-token
+// pair of G = 8 13.6 -> 10.2, one 131072-token pair (512 contributors) 95.7
+// -> 37.6.  A stage of 64 KiB instead of 32 per group saves another 5 us there
+// and costs every launch 0.1 us.
+template <int G>
+__device__ inline void combine_wave(const AttnParams& p, int wf, int c0, int c1, int wave, int lane,
+                                    float (*s_acc)[kStageFloats], float (*s_m)[G], float (*s_l)[G])
+{
+    constexpr int N = G * kHeadDim / 64;                       // elements per lane
+    constexpr int kLoads = (G * kHeadDim * 4 + 1023) / 1024;   // 1 KiB loads per row
+    constexpr int C = G == 8 ? 2 : 4;                          // rows in flight (the stage holds them)
+    static_assert(C * kLoads * 256 <= kStageFloats && G * kHeadDim <= kStageFloats, "the stage is too small");
+    float* stage = s_acc[wave];
+    const int h = lane * N / kHeadDim, dim = lane * N % kHeadDim;
+    RowState<N> r;
+    r.M = -INFINITY;
+    r.den = 0.f;
+    r.num = 0.f;
+    for (; c0 < c1; c0 += C) {
+        const int n = c1 - c0 < C ? c1 - c0 : C;
+        const Partials<G> ps(p, wf, c0, n);
+        u32x2 ml[C];
+#pragma unroll
+        for (int j = 0; j < C; ++j) {
+            ml[j] = __builtin_amdgcn_raw_buffer_load_b64(ps.ml, h * 8 + ps.slot(j) * ps.kMl, 0, kCoherentLoad);
+            if (j < n) {
+#pragma unroll
+                for (int k = 0; k < kLoads; ++k)
+                    load_to_lds(ps.acc, stage + (j * kLoads + k) * 256, lane * 16 + k * 1024 + ps.slot(j) * ps.kRow);
+            }
+        }
+        __builtin_amdgcn_s_waitcnt(0);
+        __builtin_amdgcn_sched_barrier(0);
+        asm volatile("" ::: "memory");
+        float cf[C];
+        fold_sums<N, C>(ml, n, r, cf);
+#pragma unroll
+        for (int j = 0; j < C; ++j) {
+            if (j < n) {
+#pragma unroll
+                for (int i = 0; i < N; ++i)
+                    r.num[i] = fmaf(cf[j], stage[j * kLoads * 256 + lane * N + i], r.num[i]);
+            }
+        }
+    }
+#pragma unroll
+    for (int i = 0; i < N; ++i) stage[lane * N + i] = r.num[i];
+    if (dim == 0) {
+        s_m[wave][h] = r.M;
+        s_l[wave][h] = r.den;
+    }
 }
 
 template <int G, bool kCheck, bool kAppend>
@@ -669,7 +863,7 @@ __global__ __launch_bounds__(kAttnThreads) __attribute__((amdgpu_waves_per_eu(2)
                                                         const int32_t* __restrict__ lens)
 {
     constexpr int D = kHeadDim;
-    __shared__ float s_acc[kWaves][G][D];
+    __shared__ __align__(16) float s_acc[kWaves][kStageFloats];   // a wave's state: its first G * D floats
     __shared__ float s_m[kWaves][G];
     __shared__ float s_l[kWaves][G];
     __shared__ int s_lens[kCachedLens];
@@ -973,9 +1167,9 @@ __global__ __launch_bounds__(kAttnThreads) __attribute__((amdgpu_waves_per_eu(2)
                              lane);
         // the pair's first and last work groups: this one, unless the range
         // cuts the pair (found here, while the loads are in flight)
-        const int64_t wf = blk == 0 ? w : (int64_t)uniform((int)worker_of(vf, V, W));
-        const int64_t wl = blk + take == nb ? w : (int64_t)uniform((int)worker_of(vf + nb - 1, V, W));
-        NewTokenElems ne;
+        const int wf = blk == 0 ? (int)w : uniform((int)worker_of(vf, V, W));
+        const int wl = blk + take == nb ? (int)w : uniform((int)worker_of(vf + nb - 1, V, W));
+        NewTokenElems<kEmitElems<G>> ne;
         wave_attend<G, kCheck, kAppend>(p, cs, ns, bt,
                                         more && take >= kPrefetchBlocks && take2 >= kPrefetchBlocks, L,
                                         st, wave, lane, s_acc, s_m, s_l, s_new,
@@ -990,30 +1184,26 @@ __global__ __launch_bounds__(kAttnThreads) __attribute__((amdgpu_waves_per_eu(2)
 
         // 3. merge the waves, emit rows or a partial
         const int64_t slot = partial_slot(w, wf);
-        for (int idx = tid; idx < G * D; idx += kAttnThreads) {
-            const int h = idx / D, dim = idx % D;
-            float M = s_m[0][h];
-#pragma unroll
-            for (int q = 1; q < kWaves; ++q) M = fmaxf(M, s_m[q][h]);
-            const float Ms = M == -INFINITY ? 0.f : M;
-            float num = 0.f, den = 0.f;
-#pragma unroll
-            for (int q = 0; q < kWaves; ++q) {
-                const float f = exp2_fast(s_m[q][h] - Ms);
-                num = fmaf(f, s_acc[q][h][dim], num);
-                den = fmaf(f, s_l[q][h], den);
+        constexpr int N = kEmitElems<G>;
+        const int h = tid * N / D, dim = tid * N % D;
+        const bool emits = G >= 2 || tid < D;
+        auto emit = [&](RowState<N>& r) {
+            if (append) {
+                fold_new_token<N>(s_new[h], ne.vn, r);
+                if (h == 0) store_new_token<kCheck, N>(p, ne, g, L + 1, dim);
             }
+            write_row<N>(p, b, g * G + h, dim, r);
+        };
+        if (emits) {
+            RowState<N> r = merge_waves<G, N>(s_acc, s_m, s_l, h, dim);
             if (wf == wl) {
-                if (append) {
-                    fold_new_token(s_new[h], (float)ne.vn, M, num, den);
-                    if (h == 0) store_new_token<kCheck>(p, ne, g, L + 1, dim);
-                }
-                write_row(p, b, g * G + h, dim, M, num, den);
+                emit(r);
             } else {
-                store_coherent(&p.pacc[((size_t)slot * G + h) * D + dim], num);
+#pragma unroll
+                for (int i = 0; i < N; ++i) store_coherent(&p.pacc[((size_t)slot * G + h) * D + dim + i], r.num[i]);
                 if (dim == 0) {
-                    store_coherent(&p.pml[((size_t)slot * G + h) * 2 + 0], M);
-                    store_coherent(&p.pml[((size_t)slot * G + h) * 2 + 1], den);
+                    store_coherent(&p.pml[((size_t)slot * G + h) * 2 + 0], r.M);
+                    store_coherent(&p.pml[((size_t)slot * G + h) * 2 + 1], r.den);
                 }
             }
         }
@@ -1030,56 +1220,37 @@ __global__ __launch_bounds__(kAttnThreads) __attribute__((amdgpu_waves_per_eu(2)
             if (tid == 0) {
                 int32_t* cnt = &p.counters[(size_t)b * p.Hkv + g];
                 const int old = __hip_atomic_fetch_add(cnt, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                const int last = old == (int)(wl - wf);
+                const int last = old == wl - wf;
                 if (last) __hip_atomic_store(cnt, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                 s_last = last;
             }
             __syncthreads();
             if (s_last) {
-                // combine the pair's partials: each thread issues the loads of
-                // kCombineChunk contributors at once, then folds them in with
-                // an online rescale (running max M, numerator, denominator)
-                const int nc = (int)(wl - wf + 1);
-                // the first contributor's slot is 2wf + 1; every later one
-                // starts inside the pair, so its slot is 2v (partial_slot)
-                const int64_t first_slot = partial_slot(wf, wf);
-                for (int idx = tid; idx < G * D; idx += kAttnThreads) {
-                    const int h = idx / D, dim = idx % D;
-                    float M = -INFINITY, num = 0.f, den = 0.f;
-                    for (int c0 = 0; c0 < nc; c0 += kCombineChunk) {
-                        float cm[kCombineChunk], cl[kCombineChunk], ca[kCombineChunk];
-#pragma unroll
-                        for (int j = 0; j < kCombineChunk; ++j) {
-                            cm[j] = -INFINITY;
-                            cl[j] = 0.f;
-                            ca[j] = 0.f;
-                            if (c0 + j < nc) {
-                                const int64_t sq = c0 + j == 0 ? first_slot : 2 * (wf + c0 + j);
-                                cm[j] = load_coherent(&p.pml[((size_t)sq * G + h) * 2]);
-                                cl[j] = load_coherent(&p.pml[((size_t)sq * G + h) * 2 + 1]);
-                                ca[j] = load_coherent(&p.pacc[((size_t)sq * G + h) * D + dim]);
-                            }
-                        }
-                        float Mn = M;
-#pragma unroll
-                        for (int j = 0; j < kCombineChunk; ++j) Mn = fmaxf(Mn, cm[j]);
-                        const float Ms = Mn == -INFINITY ? 0.f : Mn;
-                        const float r = exp2_fast(M - Ms);
-                        num *= r;
-                        den *= r;
-#pragma unroll
-                        for (int j = 0; j < kCombineChunk; ++j) {
-                            const float f = exp2_fast(cm[j] - Ms);
-                            num = fmaf(f, ca[j], num);
-                            den = fmaf(f, cl[j], den);
-                        }
-                        M = Mn;
+                // combine the pair's partials: a few by the threads that own
+                // the output elements, more by the four waves, whose states
+                // are then merged like those of a segment
+                const int nc = wl - wf + 1;
+                RowState<N> r;
+                r.M = -INFINITY;
+                r.den = 0.f;
+                r.num = 0.f;
+                if (nc <= kFewPartials) {
+                    if (emits) {
+                        if (nc <= 2)
+                            combine_few<G, N, 2>(p, wf, nc, tid * N, h, r);
+                        else
+                            combine_few<G, N, kFewPartials>(p, wf, nc, tid * N, h, r);
+                        emit(r);
                     }
-                    if (append) {
-                        fold_new_token(s_new[h], (float)ne.vn, M, num, den);
-                        if (h == 0) store_new_token<kCheck>(p, ne, g, L + 1, dim);
+                } else {
+                    const int per = (nc + kWaves - 1) / kWaves;
+                    const int c0 = uniform(wave) * per;
+                    combine_wave<G>(p, wf, c0, c0 + per < nc ? c0 + per : nc, uniform(wave), lane, s_acc, s_m, s_l);
+                    __syncthreads();
+                    if (emits) {
+                        r = merge_waves<G, N>(s_acc, s_m, s_l, h, dim);
+                        emit(r);
                     }
-                    write_row(p, b, g * G + h, dim, M, num, den);
                 }
             }
         }
@@ -1119,11 +1290,15 @@ __global__ __launch_bounds__(kAttnThreads) __attribute__((amdgpu_waves_per_eu(2)
                 }
             }
             for (int i = tid; i < p.Hkv * D; i += kAttnThreads)
-                store_new_token<kCheck>(
-                    p, load_new_token_elems<kCheck>(p, bt + (size_t)b * stride, bt, b, i / D, 1, i % D), i / D, 1,
+                store_new_token<kCheck, 1>(
+                    p, load_new_token_elems<kCheck, 1>(p, bt + (size_t)b * stride, bt, b, i / D, 1, i % D), i / D, 1,
                     i % D);
         } else {
-            for (int i = tid; i < p.Hq * D; i += kAttnThreads) write_row(p, b, i / D, i % D, 0.f, 0.f, 0.f);
+            RowState<1> r;
+            r.M = 0.f;
+            r.den = 0.f;
+            r.num = 0.f;
+            for (int i = tid; i < p.Hq * D; i += kAttnThreads) write_row<1>(p, b, i / D, i % D, r);
         }
     }
 #ifdef APEX_TRACE_WORK_GROUPS

@@ -44,3 +44,22 @@ def test_partition_forms_agree(torch_cuda, apex, oracle_mod, B, Hq, Hkv):  # noq
             more = run_gpu(torch_cuda, apex, padded, num_workers=workers)
             assert np.array_equal(more[:B].view(np.uint16), got.view(np.uint16)), f"padded to {pad_to}"
             assert np.all(more[B:] == 0)
+
+
+@pytest.mark.parametrize("G", [1, 2, 4, 8])
+@pytest.mark.parametrize("workers", [2, 3, 4, 5, 15, 16, 17, 33, 130])
+def test_combine_of_a_split_pair(torch_cuda, apex, oracle_mod, G, workers):  # noqa: F811
+    """One pair on `workers` work groups (one unit and a bit each): every count
+    around what the emitting threads combine on their own (4) and around what
+    four waves hold in flight at once (8 or 16), several rounds beyond it."""
+    torch = torch_cuda
+    L = 16 * workers + 5
+    case = W.make_host_case([L], G, 1, seed=workers * 8 + G, poison=True)
+    assert int(apex.plan_host([L], 1, workers, forced=True)["contributors"].max()) == workers
+    ref, lse_ref = oracle_mod.decode_attention_f64(case.q, case.k_cache, case.v_cache, case.block_table,
+                                                   case.context_lens, case.scale, return_lse=True)
+    lse = torch.zeros((1, G), dtype=torch.float32, device="cuda")
+    got = run_gpu(torch_cuda, apex, case, num_workers=workers, lse_out=lse)
+    assert_parity(got, ref, f"G={G}, {workers} contributors")
+    # fp32 sums of L <= 2085 weights and one logarithm
+    assert np.abs(lse.cpu().numpy() - lse_ref).max() <= 1e-5
