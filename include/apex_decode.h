@@ -117,7 +117,8 @@ typedef struct apex_decode_args {
      * run of short pairs is spread over several work groups); about 16 units
      * per work group, but never fewer work groups than non-empty pairs, and a
      * batch of at most one pair per CU (and at most 1024 units per CU) uses
-     * one work group per CU.  With n > 0 the ranges hold equal numbers of
+     * one work group per CU; a small batch is cut by pairs instead
+     * (apex_decode_plan_pairs_host).  With n > 0 the ranges hold equal numbers of
      * units, at least one each (tests use this to force split requests) */
     int num_workers;
     /* caller-owned device workspace of at least apex_decode_workspace_bytes()
@@ -205,7 +206,8 @@ size_t apex_decode_counter_bytes(int B, int Hkv);
 
 /*
  * Host mirror of the work partition, for inspection and tests (no GPU
- * needed).  Inputs: host context_lens[B], Hkv, block_size, the number of
+ * needed); the pair cut of small batches is apex_decode_plan_pairs_host's.
+ * Inputs: host context_lens[B], Hkv, block_size, the number of
  * launched work groups, whether that number was forced (num_workers > 0 in
  * apex_decode_args: forced grids cut equal units, the default grid equal
  * costs), and the device's compute units (the default grid uses only one
@@ -219,6 +221,23 @@ size_t apex_decode_counter_bytes(int B, int Hkv);
 int apex_decode_plan_host(const int32_t* context_lens, int B, int Hkv, int block_size,
                           int launched_workers, int forced, int cus, int32_t* contributors_out,
                           int64_t* units_out, int64_t* active_out, int64_t* partials_out);
+
+/*
+ * Host mirror of the pair cut, which the default grid uses instead of the line
+ * of apex_decode_plan_host for a small batch: every (request, kv-head) pair is
+ * cut into equal parts (the last may be shorter), one work group each, in
+ * (request, kv-head, part) order.  It applies to at most 256 requests whose
+ * pairs fit the work groups (`cus` of them up to one pair per CU, else
+ * `launched_workers`) in parts of at most 32 units (a pair of more than 2304
+ * blocks takes longer parts).
+ * Outputs (any may be NULL): parts_out[B] and part_units_out[B] = parts of each
+ * of the request's pairs and units per part (0 for an empty request),
+ * *active_out = work groups that get units, 0 when the pair cut does not apply
+ * (then apex_decode_plan_host describes the call).
+ */
+int apex_decode_plan_pairs_host(const int32_t* context_lens, int B, int Hq, int Hkv, int block_size,
+                                int launched_workers, int cus, int32_t* parts_out,
+                                int32_t* part_units_out, int64_t* active_out);
 
 /* Waits for the current device, returns the input-check error bits that
  * checked calls on it set since the last read (0 if none), and clears them. */

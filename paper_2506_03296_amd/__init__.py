@@ -17,7 +17,7 @@ import os
 
 __all__ = [
     "ApexError", "LIB_PATH", "load_library", "decode_attention", "decode_attention_ex",
-    "workspace_bytes", "plan_host", "last_error", "release_workspace", "version",
+    "workspace_bytes", "plan_host", "plan_pairs_host", "last_error", "release_workspace", "version",
     "APEX_OK", "APEX_ERR_INVALID_ARG", "APEX_ERR_UNSUPPORTED", "APEX_ERR_OUT_OF_MEMORY",
     "APEX_ERR_HIP", "EXPORTED_SYMBOLS", "counter_bytes", "kv_append", "check_device_error",
     "FLAG_CHECK_INPUTS", "DEVICE_ERR_BLOCK_ID", "DEVICE_ERR_TABLE_ROW", "decode_attention_noalloc",
@@ -35,7 +35,7 @@ EXPORTED_SYMBOLS = (
     "apex_decode_attention", "apex_decode_attention_ex", "apex_decode_workspace_bytes",
     "apex_decode_counter_bytes", "apex_decode_plan_host", "apex_decode_last_error",
     "apex_decode_release_workspace", "apex_decode_version", "apex_kv_append",
-    "apex_decode_check_device_error", "apex_decode_attention_noalloc",
+    "apex_decode_check_device_error", "apex_decode_attention_noalloc", "apex_decode_plan_pairs_host",
 )
 FLAG_CHECK_INPUTS = 1
 DEVICE_ERR_BLOCK_ID = 1
@@ -100,6 +100,9 @@ def load_library(path=None):
     lib.apex_decode_plan_host.argtypes = [vp, i32, i32, i32, i32, i32, i32, vp,
                                           ctypes.POINTER(i64), ctypes.POINTER(i64),
                                           ctypes.POINTER(i64)]
+    lib.apex_decode_plan_pairs_host.restype = i32
+    lib.apex_decode_plan_pairs_host.argtypes = [vp, i32, i32, i32, i32, i32, i32, vp, vp,
+                                                ctypes.POINTER(i64)]
     lib.apex_decode_last_error.restype = ctypes.c_char_p
     lib.apex_decode_last_error.argtypes = []
     lib.apex_decode_release_workspace.restype = i32
@@ -323,6 +326,22 @@ def plan_host(context_lens, Hkv, launched_workers, block_size=16, forced=False, 
     _check(rc)
     return {"contributors": contrib[:B * Hkv].reshape(B, Hkv), "units": units.value,
             "active": active.value, "partials": partials.value}
+
+
+def plan_pairs_host(context_lens, Hq, Hkv, launched_workers, cus, block_size=16):
+    """Host mirror of the pair cut of small batches (no GPU).  Returns a dict
+    with 'parts' and 'part_units' (numpy int32 [B]: parts of each of a
+    request's pairs, units per part) and 'active' (0: the pair cut does not
+    apply and ``plan_host`` describes the call)."""
+    import numpy as np
+    lens = np.ascontiguousarray(np.asarray(context_lens), dtype=np.int32)
+    B = lens.shape[0]
+    parts, units = np.zeros(max(B, 1), dtype=np.int32), np.zeros(max(B, 1), dtype=np.int32)
+    active = ctypes.c_int64()
+    _check(load_library().apex_decode_plan_pairs_host(
+        lens.ctypes.data if B else None, B, Hq, Hkv, block_size, launched_workers, int(cus),
+        parts.ctypes.data, units.ctypes.data, ctypes.byref(active)))
+    return {"parts": parts[:B], "part_units": units[:B], "active": active.value}
 
 
 def kv_append(k_new, v_new, k_cache, v_cache, slot_mapping, stream=None):

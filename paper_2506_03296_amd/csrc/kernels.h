@@ -12,7 +12,8 @@
 //      is too large for it), so no planner kernel runs before it;
 //   2. walks its contiguous range of (request b, kv-head g, block) units
 //      (ranges of equal cost, a pair's cost being its blocks plus a fixed
-//      start-up charge) segment by segment.  In a segment the four waves
+//      start-up charge; for a small batch one part of one pair) segment by
+//      segment.  In a segment the four waves
 //      take the blocks of one (b, g) pair round-robin; per 16-token block a
 //      wave gathers the paged K/V rows with 128-bit loads (two blocks in
 //      flight per wave), computes the G q-heads' scores as S^T = K Q^T with
@@ -909,6 +910,7 @@ __global__ __launch_bounds__(kAttnThreads) __attribute__((amdgpu_waves_per_eu(2)
     int64_t V = 0, W = 0, v0 = 0, v1 = 0, vf = 0, stride = p.bt_stride;
     int b = 0, g = 0, blk = 0, L = 0;
     bool all_nonempty = false;
+    int part_units = 0, cut_first = 0, cut_last = 0;   // pair cut: the part's units, its pair's work groups
 
     // The prologue is serial code of every work group: no K/V byte is asked
     // for before its end, and a wave issues one instruction in four cycles at
@@ -942,13 +944,66 @@ __global__ __launch_bounds__(kAttnThreads) __attribute__((amdgpu_waves_per_eu(2)
         }
         const unsigned hi = (unsigned)wave_incl_sum((int)cost), lo = hi - cost;
         const unsigned total = (unsigned)lane_value((int)hi, 63);
-        if (stride == 0) stride = lane_value(wave_incl_max(maxb), 63);
+        const int longest = lane_value(wave_incl_max(maxb), 63);
+        if (stride == 0) stride = longest;
         nonempty = uniform(nonempty);
         all_nonempty = nonempty == B;
         const uint64_t V64 = (uint64_t)total * (unsigned)p.Hkv;
         if ((V64 >> 32) != 0 || V64 * ((unsigned)p.launched + 1ull) > 0xffffffffull) return false;
         const unsigned hk = (unsigned)p.Hkv, V32 = (unsigned)V64;
         const unsigned units = V32 - (unsigned)K * (unsigned)nonempty * hk;
+        // a small batch of the default grid is cut by pairs (plan_policy.h): one
+        // segment per work group
+        const unsigned floor_units = p.cus > 0 ? pair_cut_floor(units, (uint32_t)nonempty * hk, (uint32_t)longest,
+                                                                (uint32_t)p.cus, (uint32_t)p.launched)
+                                               : 0;
+        if (floor_units > 0) {
+            unsigned T[R], parts[R], sum = 0;
+#pragma unroll
+            for (int i = 0; i < R; ++i) {
+                T[i] = (unsigned)nbs[i];
+                parts[i] = nbs[i] > 0;
+            }
+            if (floor_units < (unsigned)longest) {
+#pragma unroll
+                for (int i = 0; i < R; ++i) {
+                    if (nbs[i] == 0) continue;
+                    T[i] = pair_part_units((uint32_t)nbs[i], floor_units, G);
+                    parts[i] = ((unsigned)nbs[i] + T[i] - 1) / T[i];
+                }
+            }
+#pragma unroll
+            for (int i = 0; i < R; ++i) sum += parts[i];
+            const unsigned phi = (unsigned)wave_incl_sum((int)sum), plo = phi - sum;
+            const uint64_t hit = __ballot(plo * hk <= (unsigned)w && (unsigned)w < phi * hk);
+            if (hit == 0) return true;   // no part is left for this work group
+            const int ln = __builtin_ctzll(hit);
+            unsigned rest = (unsigned)w - (unsigned)lane_value((int)plo, ln) * hk;
+            unsigned c = (unsigned)lane_value((int)parts[0], ln);
+            int nb = lane_value(nbs[0], ln), per = lane_value((int)T[0], ln);
+            L = lane_value(Ls[0], ln);
+            b = ln * run;
+#pragma unroll
+            for (int i = 1; i < R; ++i) {
+                if (rest >= c * hk) {
+                    rest -= c * hk;
+                    c = (unsigned)lane_value((int)parts[i], ln);
+                    nb = lane_value(nbs[i], ln);
+                    per = lane_value((int)T[i], ln);
+                    L = lane_value(Ls[i], ln);
+                    ++b;
+                }
+            }
+            g = hk <= 64 ? __popcll(__ballot((unsigned)lane < hk && (unsigned)lane * c <= rest)) - 1
+                         : uniform((int)(rest / c));
+            const int part = (int)rest - g * (int)c;
+            blk = part * per;
+            part_units = min(per, nb - blk);
+            cut_first = (int)w - part;
+            cut_last = cut_first + (int)c - 1;
+            v1 = 1;   // the group has work
+            return true;
+        }
         const unsigned W32 = clamp_workers<uint32_t>(units >> __builtin_ctz((unsigned)p.min_units), units,
                                                      (uint32_t)p.launched, (uint32_t)nonempty * hk, (uint32_t)p.cus);
         V = V32;
@@ -986,7 +1041,7 @@ __global__ __launch_bounds__(kAttnThreads) __attribute__((amdgpu_waves_per_eu(2)
     bool planned = false;
     if (B <= 64)
         planned = plan_in_wave(std::integral_constant<int, 1>());
-    else if (B <= 256)
+    else if (B <= kPairCutRequests)
         planned = plan_in_wave(std::integral_constant<int, 4>());
 
     // Larger batches (and partitions past 32 bits): context_lens is read once
@@ -1117,7 +1172,7 @@ __global__ __launch_bounds__(kAttnThreads) __attribute__((amdgpu_waves_per_eu(2)
     int nb = 0, take = 0;
     if (v0 < v1) {
         nb = (int)blocks_of(L, kBlockSize);
-        take = seg_take(nb, blk, vf);
+        take = part_units > 0 ? part_units : seg_take(nb, blk, vf);
     }
 
     if (take > 0) {
@@ -1158,7 +1213,7 @@ __global__ __launch_bounds__(kAttnThreads) __attribute__((amdgpu_waves_per_eu(2)
         // the loads of a segment that the pipeline did not run on into go out
         // before the next segment is looked up
         if (!st.prefetched) load_first_tiles<kCheck>(p, cs, bt, st, lane);
-        const bool more = advance(b2, L2, nb2, g2, blk2, vf2, take);
+        const bool more = part_units == 0 && advance(b2, L2, nb2, g2, blk2, vf2, take);
         const int take2 = more ? seg_take(nb2, blk2, vf2) : 0;
         WaveSeg ns = cs;
         ns.n = 0;
@@ -1167,8 +1222,10 @@ __global__ __launch_bounds__(kAttnThreads) __attribute__((amdgpu_waves_per_eu(2)
                              lane);
         // the pair's first and last work groups: this one, unless the range
         // cuts the pair (found here, while the loads are in flight)
-        const int wf = blk == 0 ? (int)w : uniform((int)worker_of(vf, V, W));
-        const int wl = blk + take == nb ? (int)w : uniform((int)worker_of(vf + nb - 1, V, W));
+        const int wf = part_units > 0 ? cut_first : blk == 0 ? (int)w : uniform((int)worker_of(vf, V, W));
+        const int wl = part_units > 0      ? cut_last
+                       : blk + take == nb ? (int)w
+                                          : uniform((int)worker_of(vf + nb - 1, V, W));
         NewTokenElems<kEmitElems<G>> ne;
         wave_attend<G, kCheck, kAppend>(p, cs, ns, bt,
                                         more && take >= kPrefetchBlocks && take2 >= kPrefetchBlocks, L,

@@ -1,5 +1,5 @@
-// plan_host.cpp -- host mirror of the work partition (apex_decode_plan_host in
-// include/apex_decode.h): the same plan_policy.h arithmetic the kernel's
+// plan_host.cpp -- host mirrors of the work partition (apex_decode_plan_host
+// and apex_decode_plan_pairs_host in include/apex_decode.h): the same plan_policy.h arithmetic the kernel's
 // prologue runs, over host context_lens, for inspection and tests.  Plain
 // host C++ (no HIP kernels), so it also builds with g++ under sanitizers.
 #include <stdint.h>
@@ -52,6 +52,46 @@ int apex_decode_plan_host(const int32_t* context_lens, int B, int Hkv, int block
     if (units_out) *units_out = units;
     if (active_out) *active_out = units > 0 ? W : 0;
     if (partials_out) *partials_out = partials;
+    return APEX_OK;
+}
+
+int apex_decode_plan_pairs_host(const int32_t* context_lens, int B, int Hq, int Hkv, int block_size,
+                                int launched_workers, int cus, int32_t* parts_out, int32_t* part_units_out,
+                                int64_t* active_out)
+{
+    apex::clear_error();
+    if (B < 0 || Hkv <= 0 || Hq <= 0 || Hq % Hkv != 0 || launched_workers <= 0 || cus < 0)
+        return fail(APEX_ERR_INVALID_ARG, "bad partition arguments");
+    if (B > 0 && !context_lens) return fail(APEX_ERR_INVALID_ARG, "context_lens is NULL");
+    if (block_size != apex::kBlockSize)
+        return fail(APEX_ERR_UNSUPPORTED, "block_size %d unsupported (only 16)", block_size);
+    uint64_t blocks = 0, nonempty = 0, longest = 0;
+    for (int b = 0; b < B; ++b) {
+        const uint64_t nb = (uint64_t)apex::blocks_of(context_lens[b], block_size);
+        blocks += nb;
+        nonempty += nb > 0;
+        longest = nb > longest ? nb : longest;
+    }
+    // the line's positions, whose 32-bit arithmetic the kernel's rule shares
+    const uint64_t units = blocks * (uint64_t)Hkv, pairs = nonempty * (uint64_t)Hkv;
+    const uint64_t V = units + apex::kSegmentCostUnits * pairs;
+    uint32_t floor_units = 0;
+    if (B <= apex::kPairCutRequests && cus > 0 && (V >> 32) == 0 && V * ((uint64_t)launched_workers + 1) <= 0xffffffffull)
+        floor_units = apex::pair_cut_floor((uint32_t)units, (uint32_t)pairs, (uint32_t)longest, (uint32_t)cus,
+                                           (uint32_t)launched_workers);
+    int64_t active = 0;
+    for (int b = 0; b < B; ++b) {
+        const uint32_t nb = (uint32_t)apex::blocks_of(context_lens[b], block_size);
+        uint32_t T = 0, parts = 0;
+        if (floor_units > 0 && nb > 0) {
+            T = floor_units < longest ? apex::pair_part_units(nb, floor_units, (uint32_t)(Hq / Hkv)) : nb;
+            parts = (nb + T - 1) / T;
+        }
+        active += (int64_t)parts * Hkv;
+        if (parts_out) parts_out[b] = (int32_t)parts;
+        if (part_units_out) part_units_out[b] = (int32_t)T;
+    }
+    if (active_out) *active_out = active;
     return APEX_OK;
 }
 

@@ -125,4 +125,33 @@ __host__ __device__ inline int64_t partial_slot(int64_t w, int64_t wf)
     return w == wf ? 2 * w + 1 : 2 * w;
 }
 
+// Pair cut: PAIRCUT_NOTE
+constexpr uint32_t kPairCutMaxPart = 32;
+constexpr uint32_t kWholePairUnits = 16;
+
+constexpr int kPairCutRequests = 256;   // the kernel's in-register partition, four requests per lane
+
+// Least units per part that keep the parts of all pairs within the work groups
+// (sum ceil(nb / T) <= units / T + pairs); at least `longest` (the longest
+// pair's units) = no pair is cut; 0 = the pair cut does not apply.
+__host__ __device__ inline uint32_t pair_cut_floor(uint32_t units, uint32_t pairs, uint32_t longest, uint32_t cus,
+                                                   uint32_t launched)
+{
+    const uint32_t groups = pairs <= cus ? (cus < launched ? cus : launched) : launched;
+    if (pairs == 0 || pairs > groups) return 0;
+    const uint32_t room = groups - pairs;
+    if (units > room * kPairCutMaxPart) return longest <= kPairCutMaxPart ? longest : 0;
+    if (longest <= kWholePairUnits) return longest;
+    return (units + room - 1) / room;
+}
+
+// Units per part of a pair of nb blocks (the last part may have fewer).
+__host__ __device__ inline uint32_t pair_part_units(uint32_t nb, uint32_t floor_units, uint32_t group)
+{
+    if (nb <= kWholePairUnits) return nb;
+    const uint32_t low = nb < 256 ? nb : 256;
+    const uint32_t T = (group == 8 ? 8 + low / 32 : 4 + low * 3 / 64) + (nb - low) / 128;
+    return T > floor_units ? T : floor_units;
+}
+
 }  // namespace apex

@@ -1,0 +1,46 @@
+"""Host mirror of the pair cut of small batches (no GPU): every pair's parts
+cover it, fit the work groups and keep to the largest part."""
+import numpy as np
+import pytest
+
+import paper_2506_03296_amd as A
+
+
+@pytest.mark.parametrize("seed", range(8))
+def test_parts_cover_every_pair_and_fit_the_work_groups(seed):
+    rng = np.random.default_rng(seed)
+    applied = 0
+    for _ in range(300):
+        B = int(np.exp(rng.uniform(0, np.log(300))))
+        hi = int(np.exp(rng.uniform(np.log(2), np.log(20000))))
+        lens = rng.integers(-1, hi, size=B)
+        Hkv = int(rng.choice([1, 2, 8, 16, 32, 80]))
+        G = int(rng.choice([1, 2, 4, 8]))
+        cus, launched = [(256, 512), (256, 256), (32, 64), (0, 512)][int(rng.integers(0, 4))]
+        p = A.plan_pairs_host(lens, G * Hkv, Hkv, launched, cus)
+        blocks = np.where(lens > 0, -(-lens // 16), 0)
+        pairs, units, longest = int((blocks > 0).sum()) * Hkv, int(blocks.sum()) * Hkv, int(blocks.max())
+        groups = min(cus, launched) if pairs <= cus else launched
+        fits = cus > 0 and B <= 256 and 0 < pairs <= groups and (longest <= 32 or units <= 32 * (groups - pairs))
+        assert (p["active"] > 0) == fits
+        if not fits:
+            assert not p["parts"].any()
+            continue
+        applied += 1
+        parts, T = p["parts"].astype(np.int64), p["part_units"].astype(np.int64)
+        assert p["active"] == int(parts.sum()) * Hkv <= groups
+        assert np.all((parts == 0) == (blocks == 0))
+        used = blocks > 0
+        assert np.all((parts[used] - 1) * T[used] < blocks[used])      # no empty part
+        assert np.all(parts[used] * T[used] >= blocks[used])           # nothing left over
+        assert np.all(parts[blocks <= 16] <= 1)
+    assert applied > 20
+
+
+def test_bad_arguments_are_refused():
+    for args in (([5], 8, 0, 512, 256), ([5], 7, 2, 512, 256), ([5], 8, 2, 0, 256), ([5], 8, 2, 512, -1)):
+        with pytest.raises(A.ApexError):
+            A.plan_pairs_host(*args)
+    with pytest.raises(A.ApexError):
+        A.plan_pairs_host([5], 8, 2, 512, 256, block_size=32)
+    assert A.plan_pairs_host([], 8, 2, 512, 256)["active"] == 0
