@@ -5,10 +5,18 @@
 // per cache.  A pass of a 256-lane work group covers 256 / (d / 8)
 // consecutive (token, kv-head) rows, so the reads of a wave are contiguous in
 // the new-row buffer and every write is a whole 16-byte-aligned piece of one
-// cache row; a work group makes four passes with all loads in flight before
-// the stores.
-// The slot check runs per row, so padding and out-of-pool slots cost a load
-// of the slot and nothing else.
+// cache row; a work group makes two passes with all loads in flight before the
+// stores.  The rows are asked for together with their slots, not after them; a
+// padding or out-of-pool slot only drops the store.
+//
+// A decode step's append (a few hundred rows) is bound by the launch and one
+// chain of instructions and round trips: a division per row in 64 bits and the
+// rows waiting for their slot made it 3.8 us for 32 tokens of 8 kv-heads; with
+// shifts (kPow2: vectors per row, kv-heads and block size are powers of two,
+// else 32-bit divisions where they hold the slot) it takes 2.1.  One, two,
+// four, eight rows per thread: 2.07, 2.11, 2.97, 6.5 us there and 82.6, 82.7,
+// 84.8, 140 us for 54777 tokens.  That call is bound by HBM, reads and writes
+// together: 88.4 -> 82.7 us, 5.43 TB/s.
 #include <hip/hip_runtime.h>
 
 #include <limits.h>
@@ -23,46 +31,82 @@ using apex::fail;
 
 constexpr int kAppendThreads = 256;
 constexpr int kMaxRowVecs = kAppendThreads;   // d <= 2048
-constexpr int kRowsPerThread = 4;
+constexpr int kRows = 2;                      // rows per thread
+// The cache rows are written non-temporally: the attention that reads them
+// streams past the caches.  The new rows come out of a projection that has
+// just written them, so up to half the 256 MB Infinity Cache they are read
+// through it (30082 tokens, 123 MB: 37.0 us, 45.1 non-temporally); larger ones
+// cannot have stayed there and are read past it (224 MB: 84.2 against 82.7).
+constexpr int64_t kCachedNewBytes = (int64_t)128 << 20;
 
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 
+// The shape of a call: vectors per row, rows per pass of a work group, and
+// (kPow2 builds) the logarithms of vectors per row, kv-heads and block size.
+struct AppendShape {
+    int rows, Hkv, row_vecs, rows_per_pass, block_size;
+    int vec_shift, head_shift, block_shift;
+    int64_t token_vecs, capacity;
+};
+
+template <bool kPow2, bool kStream>
 __global__ __launch_bounds__(kAppendThreads) void kv_append_kernel(
-    const u32x4* __restrict__ k_new, const u32x4* __restrict__ v_new, int64_t token_vecs,
-    u32x4* __restrict__ k_cache, u32x4* __restrict__ v_cache, const int64_t* __restrict__ slots,
-    int rows, int Hkv, int row_vecs, int rows_per_pass, int block_size, int64_t capacity)
+    const u32x4* __restrict__ k_new, const u32x4* __restrict__ v_new, u32x4* __restrict__ k_cache,
+    u32x4* __restrict__ v_cache, const int64_t* __restrict__ slots, AppendShape s)
 {
-    // a work group covers kRowsPerThread passes of rows_per_pass consecutive
-    // rows; all loads of a thread are issued before its stores
-    const int local_row = (int)threadIdx.x / row_vecs;
-    const int c = (int)threadIdx.x - local_row * row_vecs;
-    if (local_row >= rows_per_pass) return;
-    const int64_t base = (int64_t)blockIdx.x * rows_per_pass * kRowsPerThread + local_row;
-    u32x4 kv[kRowsPerThread], vv[kRowsPerThread];
-    int64_t dst[kRowsPerThread];
+    const unsigned local_row = kPow2 ? threadIdx.x >> s.vec_shift : threadIdx.x / (unsigned)s.row_vecs;
+    const unsigned c = threadIdx.x - local_row * (unsigned)s.row_vecs;
+    if (local_row >= (unsigned)s.rows_per_pass) return;
+    const int64_t base = (int64_t)blockIdx.x * s.rows_per_pass * kRows + local_row;
+    u32x4 kv[kRows], vv[kRows];
+    int64_t slot[kRows];
+    unsigned g[kRows];
 #pragma unroll
-    for (int i = 0; i < kRowsPerThread; ++i) {
-        dst[i] = -1;
-        const int64_t r64 = base + (int64_t)i * rows_per_pass;
-        if (r64 >= rows) continue;
-        const int r = (int)r64;
-        const int t = r / Hkv;
-        const int g = r - t * Hkv;
-        const int64_t slot = slots[t];
-        if (slot < 0 || slot >= capacity) continue;
-        const int64_t block = slot / block_size;
-        const int64_t pos = slot - block * block_size;
-        dst[i] = ((block * Hkv + g) * block_size + pos) * row_vecs + c;
-        const int64_t src = (int64_t)t * token_vecs + (int64_t)g * row_vecs + c;
-        kv[i] = k_new[src];
-        vv[i] = v_new[src];
+    for (int i = 0; i < kRows; ++i) {
+        slot[i] = -1;
+        const int64_t r64 = base + (int64_t)i * s.rows_per_pass;
+        if (r64 >= s.rows) continue;
+        const unsigned r = (unsigned)r64;
+        const unsigned t = kPow2 ? r >> s.head_shift : r / (unsigned)s.Hkv;
+        g[i] = r - t * (unsigned)s.Hkv;
+        slot[i] = slots[t];
+        const int64_t src = (int64_t)t * s.token_vecs + (int64_t)(g[i] * (unsigned)s.row_vecs + c);
+        kv[i] = kStream ? __builtin_nontemporal_load(&k_new[src]) : k_new[src];
+        vv[i] = kStream ? __builtin_nontemporal_load(&v_new[src]) : v_new[src];
     }
 #pragma unroll
-    for (int i = 0; i < kRowsPerThread; ++i) {
-        if (dst[i] < 0) continue;
-        k_cache[dst[i]] = kv[i];
-        v_cache[dst[i]] = vv[i];
+    for (int i = 0; i < kRows; ++i) {
+        if (slot[i] < 0 || slot[i] >= s.capacity) continue;
+        int64_t block, pos;
+        if (kPow2) {
+            block = slot[i] >> s.block_shift;
+            pos = slot[i] & (s.block_size - 1);
+        } else if (((uint64_t)slot[i] >> 32) == 0) {
+            block = (unsigned)slot[i] / (unsigned)s.block_size;
+            pos = slot[i] - block * s.block_size;
+        } else {
+            block = slot[i] / s.block_size;
+            pos = slot[i] - block * s.block_size;
+        }
+        const int64_t dst = ((block * s.Hkv + g[i]) * s.block_size + pos) * s.row_vecs + c;
+        __builtin_nontemporal_store(kv[i], &k_cache[dst]);
+        __builtin_nontemporal_store(vv[i], &v_cache[dst]);
     }
+}
+
+int log2_exact(int x)
+{
+    return x > 0 && (x & (x - 1)) == 0 ? __builtin_ctz((unsigned)x) : -1;
+}
+
+template <bool kPow2, bool kStream>
+void launch_append(const void* k_new, const void* v_new, void* k_cache, void* v_cache, const int64_t* slots,
+                   const AppendShape& s, hipStream_t stream)
+{
+    const int64_t per_group = (int64_t)s.rows_per_pass * kRows;
+    const unsigned groups = (unsigned)((s.rows + per_group - 1) / per_group);
+    kv_append_kernel<kPow2, kStream><<<groups, kAppendThreads, 0, stream>>>(
+        (const u32x4*)k_new, (const u32x4*)v_new, (u32x4*)k_cache, (u32x4*)v_cache, slots, s);
 }
 
 bool aligned(const void* p, size_t a) { return ((uintptr_t)p % a) == 0; }
@@ -113,14 +157,22 @@ extern "C" int apex_kv_append(const void* k_new, const void* v_new, int64_t new_
             return fail(APEX_ERR_INVALID_ARG, "an input overlaps a cache");
     if (num_blocks == 0) return APEX_OK;   // every slot is out of the pool
 
-    const int row_vecs = d / 8;
-    const int rows_per_pass = kAppendThreads / row_vecs;
-    const int rows = T * Hkv;
-    const int64_t rows_per_group = (int64_t)rows_per_pass * kRowsPerThread;
-    const unsigned groups = (unsigned)(((int64_t)rows + rows_per_group - 1) / rows_per_group);
-    kv_append_kernel<<<groups, kAppendThreads, 0, (hipStream_t)stream>>>(
-        (const u32x4*)k_new, (const u32x4*)v_new, stride / 8, (u32x4*)k_cache, (u32x4*)v_cache,
-        slot_mapping, rows, Hkv, row_vecs, rows_per_pass, block_size, num_blocks * block_size);
+    AppendShape s;
+    s.rows = T * Hkv;
+    s.Hkv = Hkv;
+    s.row_vecs = d / 8;
+    s.rows_per_pass = kAppendThreads / s.row_vecs;
+    s.block_size = block_size;
+    s.token_vecs = stride / 8;
+    s.capacity = num_blocks * block_size;
+    s.vec_shift = log2_exact(s.row_vecs);
+    s.head_shift = log2_exact(Hkv);
+    s.block_shift = log2_exact(block_size);
+    const bool pow2 = s.vec_shift >= 0 && s.head_shift >= 0 && s.block_shift >= 0;
+    const bool stream_in = 2 * (int64_t)s.rows * d * 2 > kCachedNewBytes;
+    const auto launch = pow2 ? (stream_in ? launch_append<true, true> : launch_append<true, false>)
+                             : (stream_in ? launch_append<false, true> : launch_append<false, false>);
+    launch(k_new, v_new, k_cache, v_cache, slot_mapping, s, (hipStream_t)stream);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return fail(APEX_ERR_HIP, "kv_append launch failed: %s", hipGetErrorString(e));
     return APEX_OK;

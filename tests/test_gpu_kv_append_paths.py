@@ -1,0 +1,43 @@
+"""The append's builds (shifts or divisions, new rows read through the caches or
+past them) at the edges of each, bit for bit against the row scatter."""
+import numpy as np
+import pytest
+
+import apex_workloads as W
+from oracle import kv_cache
+from test_gpu_kv_append import apex, assert_bitwise, run_append, torch_cuda  # noqa: F401  (fixtures)
+
+pytestmark = pytest.mark.gpu
+
+# (T, NB, Hkv, d, bs): rows around one and two passes of a work group, and each
+# of vectors per row, kv-heads and block size not a power of two
+SHAPES = [(1, 1, 1, 128, 16), (2, 2, 8, 128, 16), (3, 2, 8, 128, 16), (4, 2, 8, 128, 16), (5, 2, 8, 128, 16),
+          (9, 3, 5, 128, 16), (40, 7, 8, 128, 12), (40, 7, 8, 40, 16), (41, 9, 6, 24, 10), (3, 4, 1, 2048, 16),
+          (7, 9, 1, 2040, 7)]
+
+
+@pytest.mark.parametrize("T,NB,Hkv,d,bs", SHAPES)
+def test_row_counts_and_shapes(torch_cuda, apex, T, NB, Hkv, d, bs):  # noqa: F811
+    c = W.make_append_case(T, NB, Hkv, d, bs, seed=T + d, padding=int(T > 2), out_of_range=int(T > 2))
+    gk, gv = run_append(torch_cuda, apex, c)
+    rk, rv = kv_cache.kv_append(c.k_cache, c.v_cache, c.k_new, c.v_new, c.slot_mapping)
+    assert_bitwise(gk, rk, "k")
+    assert_bitwise(gv, rv, "v")
+
+
+# rows around 128 MiB of new K and V, where they are read past the caches
+@pytest.mark.parametrize("T,Hkv,d,bs", [(16384, 1, 2048, 16), (16385, 1, 2048, 16), (5500, 6, 1024, 10)])
+def test_large_appends(torch_cuda, apex, T, Hkv, d, bs):  # noqa: F811
+    torch = torch_cuda
+    g = torch.Generator(device="cuda").manual_seed(T)
+    NB = -(-T // bs) + 3
+    kv = torch.randint(0, 1 << 15, (T, 2, Hkv, d), generator=g, device="cuda", dtype=torch.int16).view(torch.float16)
+    slots = torch.randperm(NB * bs, generator=g, device="cuda")[:T]
+    slots[::97] = -1
+    caches = [torch.full((NB, Hkv, bs, d), 7, dtype=torch.int16, device="cuda").view(torch.float16) for _ in range(2)]
+    apex.kv_append(kv[:, 0], kv[:, 1], caches[0], caches[1], slots)
+    used = slots >= 0
+    for i in range(2):
+        want = torch.full((NB, Hkv, bs, d), 7, dtype=torch.int16, device="cuda")
+        want[slots[used] // bs, :, slots[used] % bs] = kv[:, i].view(torch.int16)[used]
+        assert torch.equal(caches[i].view(torch.int16), want)
