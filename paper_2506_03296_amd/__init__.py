@@ -135,14 +135,6 @@ def release_workspace():
     _check(load_library().apex_decode_release_workspace())
 
 
-def _ptr(t):
-    return None if t is None else ctypes.c_void_p(t.data_ptr())
-
-
-def _addr(t):
-    return None if t is None else int(t.data_ptr())
-
-
 def _event_handle(ev, stream):
     """Raw hipEvent_t of a torch.cuda.Event (created on first use)."""
     if not ev.cuda_event:
@@ -153,10 +145,6 @@ def _event_handle(ev, stream):
 def _stream_obj(stream, device):
     import torch
     return stream if stream is not None else torch.cuda.current_stream(device)
-
-
-def _stream_handle(stream, device):
-    return ctypes.c_void_p(_stream_obj(stream, device).cuda_stream)
 
 
 def _require(t, name, dtype, device, shape=None, contiguous=True):
@@ -205,21 +193,78 @@ def _check_tensors(q, k_cache, v_cache, block_table, context_lens, out, block_ta
     return B, Hq, Hkv, d, bs
 
 
+# The checks above cost about 5 us of Python in a call of 10, more than the
+# kernel of a small batch takes.  The functions below answer the common case --
+# everything as it must be -- with a few attribute reads (a call is enqueued in
+# 6.3 us, without allocation in 5.4); anything else goes through the checks,
+# which raise what they find.
+
+_TORCH = None
+
+
+def _torch():
+    global _TORCH
+    if _TORCH is None:
+        import torch
+        _TORCH = torch
+    return _TORCH
+
+
+def _plain(q, k_cache, v_cache, block_table, context_lens, out):
+    """(B, Hq, Hkv, d, block_size, device index) if _check_tensors accepts the
+    tensors for sure, else None."""
+    torch = _torch()
+    f16, i32 = torch.float16, torch.int32
+    qs, ks, bs = q.shape, k_cache.shape, block_table.shape
+    if (len(qs) == 3 and len(ks) == 4 and len(bs) == 2 and q.is_cuda and qs[2] == ks[3] and bs[0] == qs[0]
+            and context_lens.shape == (qs[0],) and v_cache.shape == ks and (out is None or out.shape == qs)
+            and q.dtype is f16 and k_cache.dtype is f16 and v_cache.dtype is f16 and block_table.dtype is i32
+            and context_lens.dtype is i32 and (out is None or out.dtype is f16)):
+        i = q.get_device()
+        if (k_cache.get_device() == i and v_cache.get_device() == i and block_table.get_device() == i
+                and context_lens.get_device() == i and (out is None or out.get_device() == i)
+                and q.is_contiguous() and k_cache.is_contiguous() and v_cache.is_contiguous()
+                and block_table.is_contiguous() and context_lens.is_contiguous()
+                and (out is None or out.is_contiguous())):
+            return qs[0], qs[1], ks[1], qs[2], ks[2], i
+    return None
+
+
+def _dims(q, k_cache, v_cache, block_table, context_lens, out, block_table_stride=0):
+    dims = _plain(q, k_cache, v_cache, block_table, context_lens, out)
+    if dims is None or (block_table_stride and block_table.shape[1] != block_table_stride):
+        dims = (*_check_tensors(q, k_cache, v_cache, block_table, context_lens, out, block_table_stride),
+                q.get_device())
+    return dims
+
+
+def _raw_stream(stream, index):
+    """hipStream_t of a torch stream (default: the device's current one)."""
+    if stream is not None:
+        return stream.cuda_stream
+    return _torch()._C._cuda_getCurrentRawStream(index)
+
+
+def _on(t, dtype, index):
+    """True if t is a tensor of this dtype on GPU `index`."""
+    return t.dtype is dtype and t.is_cuda and t.get_device() == index
+
+
 def decode_attention(q, k_cache, v_cache, block_table, context_lens, scale, out=None,
                      stream=None):
     """apex_decode_attention over torch tensors; returns ``out``.
 
     The block table must be tight ([B][ceil(max L / 16)]); use
     ``decode_attention_ex`` for wider rows."""
-    import torch
-    B, Hq, Hkv, d, bs = _check_tensors(q, k_cache, v_cache, block_table, context_lens, out)
+    B, Hq, Hkv, d, bs, index = _dims(q, k_cache, v_cache, block_table, context_lens, out)
     if out is None:
-        out = torch.empty((B, Hq, d), dtype=torch.float16, device=q.device)
-    lib = load_library()
-    rc = lib.apex_decode_attention(_ptr(q), _ptr(k_cache), _ptr(v_cache), _ptr(block_table),
-                                   _ptr(context_lens), _ptr(out), B, Hq, Hkv, d, bs,
-                                   ctypes.c_float(scale), _stream_handle(stream, q.device))
-    _check(rc)
+        out = _torch().empty((B, Hq, d), dtype=q.dtype, device=q.device)
+    rc = load_library().apex_decode_attention(
+        q.data_ptr(), k_cache.data_ptr(), v_cache.data_ptr(), block_table.data_ptr(), context_lens.data_ptr(),
+        out.data_ptr(), B, Hq, Hkv, d, bs, ctypes.c_float(scale),
+        _raw_stream(stream, index))
+    if rc:
+        _check(rc)
     return out
 
 
@@ -230,12 +275,13 @@ def decode_attention_noalloc(q, k_cache, v_cache, block_table, context_lens, sca
     table must be tight, as for ``decode_attention``."""
     if out is None:
         raise ValueError("decode_attention_noalloc writes into the caller's out")
-    B, Hq, Hkv, d, bs = _check_tensors(q, k_cache, v_cache, block_table, context_lens, out)
-    lib = load_library()
-    rc = lib.apex_decode_attention_noalloc(_ptr(q), _ptr(k_cache), _ptr(v_cache), _ptr(block_table),
-                                           _ptr(context_lens), _ptr(out), B, Hq, Hkv, d, bs,
-                                           ctypes.c_float(scale), _stream_handle(stream, q.device))
-    _check(rc)
+    B, Hq, Hkv, d, bs, index = _dims(q, k_cache, v_cache, block_table, context_lens, out)
+    rc = load_library().apex_decode_attention_noalloc(
+        q.data_ptr(), k_cache.data_ptr(), v_cache.data_ptr(), block_table.data_ptr(), context_lens.data_ptr(),
+        out.data_ptr(), B, Hq, Hkv, d, bs, ctypes.c_float(scale),
+        _raw_stream(stream, index))
+    if rc:
+        _check(rc)
     return out
 
 
@@ -253,29 +299,25 @@ def decode_attention_ex(q, k_cache, v_cache, block_table, context_lens, scale, o
     ``k_new``/``v_new`` (fp16 [B][Hkv][d], unit strides inside a token) turn
     on the fused append: the current token (position L - 1) is attended from
     them and written to its cache slot in the same launch."""
-    import torch
-    B, Hq, Hkv, d, bs = _check_tensors(q, k_cache, v_cache, block_table, context_lens, out,
-                                       block_table_stride)
+    torch = _torch()
+    B, Hq, Hkv, d, bs, index = _dims(q, k_cache, v_cache, block_table, context_lens, out, block_table_stride)
     if out is None:
         out = torch.empty((B, Hq, d), dtype=torch.float16, device=q.device)
-    if lse_out is not None:
+    if lse_out is not None and not (lse_out.shape == (B, Hq) and _on(lse_out, torch.float32, index)
+                                    and lse_out.is_contiguous()):
         _require(lse_out, "lse_out", torch.float32, q.device, shape=(B, Hq))
-    if workspace is not None:
+    if workspace is not None and not (_on(workspace, torch.uint8, index) and workspace.is_contiguous()):
         _require(workspace, "workspace", torch.uint8, q.device)
-    a = DecodeArgs()
-    a.q, a.k_cache, a.v_cache = _addr(q), _addr(k_cache), _addr(v_cache)
-    a.block_table, a.context_lens, a.out = _addr(block_table), _addr(context_lens), _addr(out)
-    a.B, a.Hq, a.Hkv, a.d, a.block_size = B, Hq, Hkv, d, bs
-    a.scale = float(scale)
-    s = _stream_obj(stream, q.device)
-    a.stream = int(s.cuda_stream)
-    a.block_table_stride = int(block_table_stride)
-    a.num_workers = int(num_workers)
+    a = DecodeArgs(q.data_ptr(), k_cache.data_ptr(), v_cache.data_ptr(), block_table.data_ptr(),
+                   context_lens.data_ptr(), out.data_ptr(), B, Hq, Hkv, d, bs, float(scale),
+                   int(_raw_stream(stream, index)), int(block_table_stride), int(num_workers))
     if workspace is not None:
-        a.workspace = _addr(workspace)
-        a.workspace_bytes = workspace.numel() * workspace.element_size()
-    a.lse_out = _addr(lse_out)
+        a.workspace = workspace.data_ptr()
+        a.workspace_bytes = workspace.numel()
+    if lse_out is not None:
+        a.lse_out = lse_out.data_ptr()
     if events is not None:
+        s = _stream_obj(stream, q.device)
         a.attn_kernel_events[0] = _event_handle(events[0], s)
         a.attn_kernel_events[1] = _event_handle(events[1], s)
     if check_inputs:
@@ -284,13 +326,16 @@ def decode_attention_ex(q, k_cache, v_cache, block_table, context_lens, scale, o
     if k_new is not None or v_new is not None:
         if k_new is None or v_new is None or k_new.shape != (B, Hkv, d) or v_new.shape != k_new.shape:
             raise ValueError("k_new and v_new must both be [B][Hkv][d]")
-        _require(k_new, "k_new", torch.float16, q.device, contiguous=False)
-        _require(v_new, "v_new", torch.float16, q.device, contiguous=False)
-        if k_new.stride(2) != 1 or k_new.stride(1) != d or v_new.stride() != k_new.stride():
+        if not (_on(k_new, torch.float16, index) and _on(v_new, torch.float16, index)):
+            _require(k_new, "k_new", torch.float16, q.device, contiguous=False)
+            _require(v_new, "v_new", torch.float16, q.device, contiguous=False)
+        strides = k_new.stride()
+        if strides[2] != 1 or strides[1] != d or v_new.stride() != strides:
             raise ValueError("k_new/v_new need unit strides inside a token and equal strides")
-        a.k_new, a.v_new = _addr(k_new), _addr(v_new)
-        a.new_token_stride = int(k_new.stride(0))
-    _check(load_library().apex_decode_attention_ex(ctypes.byref(a)))
+        a.k_new, a.v_new, a.new_token_stride = k_new.data_ptr(), v_new.data_ptr(), strides[0]
+    rc = load_library().apex_decode_attention_ex(ctypes.byref(a))
+    if rc:
+        _check(rc)
     return out
 
 
@@ -357,22 +402,26 @@ def kv_append(k_new, v_new, k_cache, v_cache, slot_mapping, stream=None):
     nb, hkv2, bs, d2 = k_cache.shape
     if (hkv2, d2) != (Hkv, d) or v_cache.shape != k_cache.shape:
         raise ValueError("new rows and caches disagree on Hkv or d")
-    for t in (k_new, v_new):
-        if t.stride(2) != 1 or t.stride(1) != d:
-            raise ValueError("each token's rows must be contiguous [Hkv][d]")
-    if T > 1 and k_new.stride(0) != v_new.stride(0):
+    ks, vs = k_new.stride(), v_new.stride()
+    if ks[2] != 1 or ks[1] != d or vs[2] != 1 or vs[1] != d:
+        raise ValueError("each token's rows must be contiguous [Hkv][d]")
+    if T > 1 and ks[0] != vs[0]:
         raise ValueError("k_new and v_new must share the token stride")
-    import torch
-    dev = k_cache.device
-    if dev.type != "cuda":
-        raise ValueError(f"the caches must be GPU tensors, got {dev}")
-    _require(k_cache, "k_cache", torch.float16, dev)
-    _require(v_cache, "v_cache", torch.float16, dev)
-    _require(k_new, "k_new", torch.float16, dev, contiguous=False)
-    _require(v_new, "v_new", torch.float16, dev, contiguous=False)
-    _require(slot_mapping, "slot_mapping", torch.int64, dev, shape=(T,))
-    stride = k_new.stride(0) if T > 1 else 0
-    rc = load_library().apex_kv_append(_ptr(k_new), _ptr(v_new), stride, _ptr(k_cache),
-                                       _ptr(v_cache), _ptr(slot_mapping), T, Hkv, d, bs, nb,
-                                       _stream_handle(stream, k_cache.device))
-    _check(rc)
+    torch = _torch()
+    f16, index = torch.float16, k_cache.get_device()
+    if not (_on(k_cache, f16, index) and _on(v_cache, f16, index) and _on(k_new, f16, index)
+            and _on(v_new, f16, index) and _on(slot_mapping, torch.int64, index) and slot_mapping.shape == (T,)
+            and k_cache.is_contiguous() and v_cache.is_contiguous() and slot_mapping.is_contiguous()):
+        dev = k_cache.device
+        if dev.type != "cuda":
+            raise ValueError(f"the caches must be GPU tensors, got {dev}")
+        _require(k_cache, "k_cache", f16, dev)
+        _require(v_cache, "v_cache", f16, dev)
+        _require(k_new, "k_new", f16, dev, contiguous=False)
+        _require(v_new, "v_new", f16, dev, contiguous=False)
+        _require(slot_mapping, "slot_mapping", torch.int64, dev, shape=(T,))
+    rc = load_library().apex_kv_append(
+        k_new.data_ptr(), v_new.data_ptr(), ks[0] if T > 1 else 0, k_cache.data_ptr(), v_cache.data_ptr(),
+        slot_mapping.data_ptr(), T, Hkv, d, bs, nb, _raw_stream(stream, index))
+    if rc:
+        _check(rc)
