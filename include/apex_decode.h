@@ -117,8 +117,8 @@ typedef struct apex_decode_args {
      * run of short pairs is spread over several work groups); about 16 units
      * per work group, but never fewer work groups than non-empty pairs, and a
      * batch of at most one pair per CU (and at most 1024 units per CU) uses
-     * one work group per CU; a small batch is cut by pairs instead
-     * (apex_decode_plan_pairs_host).  With n > 0 the ranges hold equal numbers of
+     * one work group per CU; small batches and many short pairs are
+     * partitioned by pairs instead (apex_decode_plan_pairs_host).  With n > 0 the ranges hold equal numbers of
      * units, at least one each (tests use this to force split requests) */
     int num_workers;
     /* caller-owned device workspace of at least apex_decode_workspace_bytes()
@@ -206,7 +206,7 @@ size_t apex_decode_counter_bytes(int B, int Hkv);
 
 /*
  * Host mirror of the work partition, for inspection and tests (no GPU
- * needed); the pair cut of small batches is apex_decode_plan_pairs_host's.
+ * needed); the partitions by pairs are apex_decode_plan_pairs_host's.
  * Inputs: host context_lens[B], Hkv, block_size, the number of
  * launched work groups, whether that number was forced (num_workers > 0 in
  * apex_decode_args: forced grids cut equal units, the default grid equal
@@ -223,17 +223,21 @@ int apex_decode_plan_host(const int32_t* context_lens, int B, int Hkv, int block
                           int64_t* units_out, int64_t* active_out, int64_t* partials_out);
 
 /*
- * Host mirror of the pair cut, which the default grid uses instead of the line
- * of apex_decode_plan_host for a small batch: every (request, kv-head) pair is
- * cut into equal parts (the last may be shorter), one work group each, in
- * (request, kv-head, part) order.  It applies to at most 256 requests whose
- * pairs fit the work groups (`cus` of them up to one pair per CU, else
- * `launched_workers`) in parts of at most 32 units (a pair of more than 2304
- * blocks takes longer parts).
+ * Host mirror of the two partitions by pairs, which the default grid uses
+ * instead of the line of apex_decode_plan_host for small batches and for many
+ * short pairs.
+ * Pair cut: every (request, kv-head) pair is cut into equal parts (the last may
+ * be shorter), one work group each, in (request, kv-head, part) order.  It
+ * applies to at most 256 requests whose pairs fit the work groups (`cus` of
+ * them up to one pair per CU, else `launched_workers`) in parts of at most 32
+ * units (a pair of more than 2304 blocks takes longer parts).
+ * Short pairs: every pair is taken whole by one wave of a work group.  It
+ * applies to at most 512 requests with more pairs than work groups and at most
+ * 32 blocks each, where it is estimated to be faster.
  * Outputs (any may be NULL): parts_out[B] and part_units_out[B] = parts of each
  * of the request's pairs and units per part (0 for an empty request),
- * *active_out = work groups that get units, 0 when the pair cut does not apply
- * (then apex_decode_plan_host describes the call).
+ * *active_out = work groups that get units, 0 when neither applies (then
+ * apex_decode_plan_host describes the call).
  */
 int apex_decode_plan_pairs_host(const int32_t* context_lens, int B, int Hq, int Hkv, int block_size,
                                 int launched_workers, int cus, int32_t* parts_out,

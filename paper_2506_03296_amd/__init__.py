@@ -374,10 +374,11 @@ def plan_host(context_lens, Hkv, launched_workers, block_size=16, forced=False, 
 
 
 def plan_pairs_host(context_lens, Hq, Hkv, launched_workers, cus, block_size=16):
-    """Host mirror of the pair cut of small batches (no GPU).  Returns a dict
-    with 'parts' and 'part_units' (numpy int32 [B]: parts of each of a
-    request's pairs, units per part) and 'active' (0: the pair cut does not
-    apply and ``plan_host`` describes the call)."""
+    """Host mirror of the partitions by pairs: the pair cut of small batches
+    and whole pairs per wave for many short ones (no GPU).  Returns a dict with
+    'parts' and 'part_units' (numpy int32 [B]: parts of each of a request's
+    pairs, units per part) and 'active' (0: neither applies and ``plan_host``
+    describes the call)."""
     import numpy as np
     lens = np.ascontiguousarray(np.asarray(context_lens), dtype=np.int32)
     B = lens.shape[0]

@@ -7,12 +7,13 @@
 // group
 //   1. reads context_lens once and derives the partition of plan_policy.h on
 //      its own (block sums, a prefix scan, the longest request for the tight
-//      block-table stride; in every wave's registers for up to 256 requests,
+//      block-table stride; in every wave's registers for up to 512 requests,
 //      by the group through LDS for more; 32-bit arithmetic unless the batch
 //      is too large for it), so no planner kernel runs before it;
 //   2. walks its contiguous range of (request b, kv-head g, block) units
 //      (ranges of equal cost, a pair's cost being its blocks plus a fixed
-//      start-up charge; for a small batch one part of one pair) segment by
+//      start-up charge; for a small batch one part of one pair; with many
+//      short pairs every wave takes whole pairs of its own) segment by
 //      segment.  In a segment the four waves
 //      take the blocks of one (b, g) pair round-robin; per 16-token block a
 //      wave gathers the paged K/V rows with 128-bit loads (two blocks in
@@ -285,13 +286,13 @@ struct WaveSeg {
     int b, g;            // the pair
 };
 
-template <int G>
+template <int G, int kStep>
 __device__ inline WaveSeg wave_seg(const AttnParams& p, const int32_t* bt_row, int b, int g, int lo,
                                    int hi, int wave, int lane)
 {
     WaveSeg s;
-    s.first = uniform(lo + wave);
-    s.n = s.first < hi ? (hi - s.first + kWaves - 1) / kWaves : 0;
+    s.first = uniform(kStep == 1 ? lo : lo + wave);
+    s.n = s.first < hi ? (hi - s.first + kStep - 1) / kStep : 0;
     s.bt = bt_row + s.first;
     const size_t head_off = (size_t)uniform(g) * (kBlockSize * kHeadDim);
     s.kpair = uniform_ptr(p.k + head_off);
@@ -333,6 +334,14 @@ struct WaveTiles {
     bool prefetched;     // the tiles hold the segment's blocks 0 and 1
     f16x8 qop[4];        // Q^T of the current segment
     f16x8 qnext[4];      // Q^T of the next segment (loaded one segment ahead)
+};
+
+// A wave's attention state over its blocks: lane (h = lane % 16, q = lane / 16)
+// has head h's running max m (log2 units) and sum l of the weights of all of
+// the wave's tokens, and P.V at dims 32q + 8i + t.
+struct WaveState {
+    float m, l;
+    f32x4 acc[8];
 };
 
 // Fused append.  Scaled logits (log2 units) of the current token for the G
@@ -409,7 +418,7 @@ __device__ inline NewTokenElems<N> load_new_token_elems(const AttnParams& p, con
 
 // Issues the loads of a segment's blocks 0 and 1 (tile 0 first) and of the ids
 // that follow them, for a segment that the pipeline does not run on into.
-template <bool kCheck>
+template <bool kCheck, int kStep>
 __device__ inline void load_first_tiles(const AttnParams& p, const WaveSeg& cs, const int32_t* safe, WaveTiles& st,
                                         int lane)
 {
@@ -417,7 +426,7 @@ __device__ inline void load_first_tiles(const AttnParams& p, const WaveSeg& cs, 
     const uint32_t step = (uint32_t)((size_t)p.Hkv * kBlockSize * kHeadDim);
     const int koff = k_lane_offset(lane), voff = v_lane_offset(lane);
     auto id_at = [&](int pos) -> int {
-        const int32_t* a = pos < n ? cs.bt + kWaves * pos : safe;
+        const int32_t* a = pos < n ? cs.bt + kStep * pos : safe;
         return *(const __attribute__((address_space(4))) int32_t*)a;
     };
     auto id_ok = [&](int id) -> bool { return !kCheck || (id >= 0 && (int64_t)id < p.num_blocks); };
@@ -440,19 +449,18 @@ __device__ inline void load_first_tiles(const AttnParams& p, const WaveSeg& cs, 
 // current token for the emit).  Lane
 // (h = lane % 16, q = lane / 16) keeps m (running max of head h, log2 units,
 // equal on the four lanes of h), l (sum of the weights of its tokens) and
-// acc[t][i] (running P.V of head h at dim 32q + 8i + t).  On return the
-// wave's state is in s_acc/s_m/s_l and the tiles hold (in flight) the next
-// segment's first blocks.
-template <int G, bool kCheck, bool kAppend>
+// acc[t][i] (running P.V of head h at dim 32q + 8i + t).  The wave takes every
+// kStep-th block: kWaves when the four waves share a segment, 1 when it has one
+// of its own.  On return its state is in ws and the tiles hold (in flight) the
+// next segment's first blocks.
+template <int G, bool kCheck, bool kAppend, int kStep>
 __device__ inline void wave_attend(const AttnParams& p, const WaveSeg& cs, const WaveSeg& ns,
                                    const int32_t* safe, bool pf_next, int L, WaveTiles& st, int wave,
-                                   int lane,
-                                   float (*s_acc)[kStageFloats], float (*s_m)[G], float (*s_l)[G],
+                                   int lane, WaveState& ws,
                                    float* s_new, const int32_t* cur_row, NewTokenElems<kEmitElems<G>>& ne)
 {
     constexpr int D = kHeadDim;
     constexpr int BS = kBlockSize;
-    const int col = lane & 15;
     const int q = lane >> 4;
     const int n = cs.n;
 
@@ -467,12 +475,12 @@ __device__ inline void wave_attend(const AttnParams& p, const WaveSeg& cs, const
     // table is read-only during the call: reading it through the constant
     // address space keeps the load on the scalar path.
     auto id_at = [&](bool here, int pos, bool ok) -> int {
-        const int32_t* a = ok ? (here ? cs.bt : ns.bt) + kWaves * pos : safe;
+        const int32_t* a = ok ? (here ? cs.bt : ns.bt) + kStep * pos : safe;
         return *(const __attribute__((address_space(4))) int32_t*)a;
     };
     // the tiles continue into the next segment (the work group's choice:
     // both segments are long)
-    const bool pf = pf_next;
+    const bool pf = kStep == kWaves && pf_next;
 
     // Everything loaded before the loop (the tiles, mostly issued during the
     // previous segment's last steps, and this segment's Q^T, issued one
@@ -484,7 +492,7 @@ __device__ inline void wave_attend(const AttnParams& p, const WaveSeg& cs, const
 #endif
 #pragma unroll
     for (int i = 0; i < 4; ++i) st.qop[i] = st.qnext[i];
-    load_q<G>(st.qnext, ns, lane);   // used by the next segment only
+    if (kStep == kWaves) load_q<G>(st.qnext, ns, lane);   // used by the next segment only
     // With the fused append: the rows of the current token's logits for this
     // pair (wave 0 sums them after the loop; the merge reads them) and this
     // thread's elements for the emit.  Issued after the wait above, they
@@ -495,12 +503,13 @@ __device__ inline void wave_attend(const AttnParams& p, const WaveSeg& cs, const
     NewTokenRows<G> nt;
     if (kAppend) {
         load_new_token_rows<G>(p, cs.b, cs.g, lane, nt);
-        ne = load_new_token_elems<kCheck, kEmitElems<G>>(p, cur_row, safe, cs.b, cs.g, L + 1,
-                                                         (wave * 64 + lane) * kEmitElems<G> % D);
+        if (kStep == kWaves)
+            ne = load_new_token_elems<kCheck, kEmitElems<G>>(p, cur_row, safe, cs.b, cs.g, L + 1,
+                                                             (wave * 64 + lane) * kEmitElems<G> % D);
     }
 
     float m = -INFINITY, l = 0.f;
-    f32x4 acc[8];
+    f32x4 (&acc)[8] = ws.acc;
 #pragma unroll
     for (int t = 0; t < 8; ++t) acc[t] = f32x4{0.f, 0.f, 0.f, 0.f};
 
@@ -526,7 +535,7 @@ __device__ inline void wave_attend(const AttnParams& p, const WaveSeg& cs, const
         const f16* kbase = r_here ? cs.kpair : ns.kpair;
         const f16* vbase = r_here ? cs.vpair : ns.vpair;
         const int nbytes = r_ok && id_ok(id2) ? kSlabBytes : 0;
-        const int tok0 = (cs.first + kWaves * k) * BS;
+        const int tok0 = (cs.first + kStep * k) * BS;
         const int cur_id = cur;
         cur = id2;
         nid = id_next;
@@ -621,21 +630,85 @@ __device__ inline void wave_attend(const AttnParams& p, const WaveSeg& cs, const
     }
     if (k < n) block_step(st.kt0, st.vt0, k, st.cur0, st.nid0);
     st.prefetched = pf;
-    if (kAppend && uniform(wave) == 0) new_token_logits<G>(p, nt, lane, s_new);
+    if (kAppend && (kStep == 1 || uniform(wave) == 0)) new_token_logits<G>(p, nt, lane, s_new);
+    ws.m = m;
+    ws.l = rows_sum4(l);   // over the four token groups
+}
 
-    // the wave's state for head h: l summed over the four token groups
-    const float lw = rows_sum4(l);
+// A wave's state of a segment, to be merged with the other waves'.
+template <int G>
+__device__ inline void store_wave_state(const WaveState& ws, int wave, int lane, float (*s_acc)[kStageFloats],
+                                        float (*s_m)[G], float (*s_l)[G])
+{
+    const int col = lane & 15, q = lane >> 4;
     if (col < G) {
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
-            float* dst = &s_acc[wave][col * D + 32 * q + 8 * i];
-            *(f32x4*)dst = f32x4{acc[0][i], acc[1][i], acc[2][i], acc[3][i]};
-            *(f32x4*)(dst + 4) = f32x4{acc[4][i], acc[5][i], acc[6][i], acc[7][i]};
+            float* dst = &s_acc[wave][col * kHeadDim + 32 * q + 8 * i];
+            *(f32x4*)dst = f32x4{ws.acc[0][i], ws.acc[1][i], ws.acc[2][i], ws.acc[3][i]};
+            *(f32x4*)(dst + 4) = f32x4{ws.acc[4][i], ws.acc[5][i], ws.acc[6][i], ws.acc[7][i]};
         }
         if (q == 0) {
-            s_m[wave][col] = m;
-            s_l[wave][col] = lw;
+            s_m[wave][col] = ws.m;
+            s_l[wave][col] = ws.l;
         }
+    }
+}
+
+// A whole pair's rows from one wave's state (lane (h, q): head h, dims
+// 32q + 8i + t), with the fused append the current token's fold and store.
+template <int G, bool kCheck, bool kAppend>
+__device__ inline void emit_wave(const AttnParams& p, WaveState& ws, int b, int g, int Lc, int lane,
+                                 const float* s_new, const int32_t* bt_row, const int32_t* safe)
+{
+    const int col = lane & 15, q = lane >> 4;
+    float M = ws.m, den = ws.l;
+    if (kAppend) {
+        const size_t src = (size_t)b * p.new_stride + (size_t)g * kHeadDim;
+        f16x8 v[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) v[i] = *(const f16x8*)(p.v_new + src + 32 * q + 8 * i);
+        const float sn = s_new[col < G ? col : 0];
+        const float M2 = fmaxf(M, sn);
+        const float f = M == -INFINITY ? 0.f : exp2_fast(M - M2);
+        const float wgt = exp2_fast(sn - M2);
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+#pragma unroll
+            for (int t = 0; t < 8; ++t) ws.acc[t][i] = fmaf(wgt, (float)v[i][t], ws.acc[t][i] * f);
+        den = fmaf(den, f, wgt);
+        M = M2;
+        // lanes 0-15 store the K row, lanes 16-31 the V row
+        if (lane < 32) {
+            const NewTokenElems<8> e = load_new_token_elems<kCheck, 8>(p, bt_row, safe, b, g, Lc, 8 * col);
+            if (e.in_row && !(kCheck && !(e.id >= 0 && (int64_t)e.id < p.num_blocks))) {
+                const size_t dst =
+                    (((size_t)(uint32_t)e.id * p.Hkv + g) * kBlockSize + (Lc - 1) % kBlockSize) * kHeadDim + 8 * col;
+                *(f16x8*)&(q == 0 ? p.k_store : p.v_store)[dst] = q == 0 ? e.kn : e.vn;
+            } else if (kCheck && e.in_row && lane == 0) {
+                report_error(p, kErrBlockId);
+            }
+        }
+    }
+    if (col < G) {
+        const int head = g * G + col;
+        f16* row = p.out + ((size_t)b * p.Hq + head) * kHeadDim + 32 * q;
+        // one reciprocal per head; a quotient with one correction step is
+        // within half an ulp and a rounding of the division's
+        const float inv = den > 0.f ? 1.f / den : 0.f;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            f16x8 o;
+#pragma unroll
+            for (int t = 0; t < 8; ++t) {
+                const float a = ws.acc[t][i], y = a * inv;
+                const float z = fmaf(fmaf(-y, den, a), inv, y);
+                o[t] = (f16)(den > 0.f ? z : 0.f);
+            }
+            *(f16x8*)(row + 8 * i) = o;
+        }
+        if (p.lse && q == 0)
+            p.lse[(size_t)b * p.Hq + head] = den > 0.f ? (M + __log2f(den)) * 0.69314718055994531f : -INFINITY;
     }
 }
 
@@ -858,6 +931,17 @@ __device__ inline void combine_wave(const AttnParams& p, int wf, int c0, int c1,
     }
 }
 
+// What a wave's own partition gives a work group (all scalar).
+struct WavePlan {
+    bool planned = false;      // false: the group-wide partition decides
+    bool all_nonempty = false;
+    int short_pairs = 0;       // > 0: single waves take whole pairs, this many in all
+    int part_units = 0;        // > 0: pair cut, units of the group's part,
+    int cut_first = 0, cut_last = 0;   // and the work groups of its pair
+    int b = 0, g = 0, blk = 0, L = 0;  // the group's first segment
+    int64_t V = 0, W = 0, v0 = 0, v1 = 0, vf = 0, stride = 0;
+};
+
 template <int G, bool kCheck, bool kAppend>
 __global__ __launch_bounds__(kAttnThreads) __attribute__((amdgpu_waves_per_eu(2))) void attn_kernel(AttnParams p,
                                                         const int32_t* __restrict__ bt,
@@ -876,7 +960,8 @@ __global__ __launch_bounds__(kAttnThreads) __attribute__((amdgpu_waves_per_eu(2)
     __shared__ int s_loc_blk;
     __shared__ int64_t s_loc_vf;
     __shared__ int s_last;
-    __shared__ float s_new[G];
+    __shared__ float s_new[kWaves][G];
+    __shared__ int s_order[kShortRequests];   // the non-empty requests, in order
 
     const int tid = threadIdx.x;
     const int lane = tid & 63;
@@ -907,56 +992,72 @@ __global__ __launch_bounds__(kAttnThreads) __attribute__((amdgpu_waves_per_eu(2)
     };
     auto len_of = [&](int b) -> int { return cached ? s_lens[b] : cached_len(lens[b]); };
     const int K = p.seg_cost;
-    int64_t V = 0, W = 0, v0 = 0, v1 = 0, vf = 0, stride = p.bt_stride;
-    int b = 0, g = 0, blk = 0, L = 0;
-    bool all_nonempty = false;
-    int part_units = 0, cut_first = 0, cut_last = 0;   // pair cut: the part's units, its pair's work groups
 
     // The prologue is serial code of every work group: no K/V byte is asked
     // for before its end, and a wave issues one instruction in four cycles at
     // best, so its time is its instruction count.  For a batch of up to
-    // kLanes * R requests every wave derives the partition on its own, lane i
-    // holding R consecutive requests (R = 1 up to 64 requests, else 4): one
+    // 64 R requests every wave derives the partition on its own, lane i
+    // holding R consecutive requests (R = 1 up to 64 requests, 4 up to 256, 8 up to 512): one
     // scan of the requests' cost, ballots and lane reads, no barrier and no
     // LDS round trip, all results in scalar registers, products in 32 bits.
     // Returns false, with nothing decided, when 32 bits do not hold them
     // (plan bound: V (launched + 1) < 2^32).  Against the group-wide form
     // below, a work group's time from its start to its first segment falls
     // from 1.9 to 1.1 us for 16 requests and from 1.7 to 1.0 us for 4.
-    auto plan_in_wave = [&](auto runs) -> bool {
+    auto plan_in_wave = [&](auto runs) -> WavePlan {
         constexpr int R = decltype(runs)::value;
-        const int run = R == 1 ? 1 : (B + 63) >> 6;
-        int Ls[R], nbs[R];
+        WavePlan r;
+        int raws[R], Ls[R], nbs[R];
         unsigned cost = 0;
         int maxb = 0, nonempty = 0;
 #pragma unroll
+        for (int i = 0; i < R; ++i) raws[i] = 0;
+        if (R > 1 && lane * R + R <= B) {
+            // (context_lens is 4-byte aligned; such vector loads are allowed)
+            typedef int i32x4_any __attribute__((ext_vector_type(4), aligned(4)));
+#pragma unroll
+            for (int i = 0; i + 3 < R; i += 4) {
+                const i32x4_any v = *(const i32x4_any*)(lens + lane * R + i);
+                raws[i] = v[0];
+                raws[i + 1] = v[1];
+                raws[i + 2] = v[2];
+                raws[i + 3] = v[3];
+            }
+        } else if (lane * R < B) {
+#pragma unroll
+            for (int i = 0; i < R; ++i)
+                if (lane * R + i < B) raws[i] = lens[lane * R + i];
+        }
+#pragma unroll
         for (int i = 0; i < R; ++i) {
-            const int r = lane * run + i;
-            const bool in = i < run && r < B;
-            const int raw = in ? lens[r] : 0;
-            if (in && is_cut(raw)) report_error(p, kErrTableRow);
+            const int raw = raws[i];
+            if (is_cut(raw)) report_error(p, kErrTableRow);
             Ls[i] = cached_len(raw);
-            nbs[i] = (int)blocks_of(Ls[i], kBlockSize);
-            maxb = max(maxb, (int)blocks_of(is_cut(raw) ? (int)row_tokens : raw, kBlockSize));
+            // blocks_of in 32 bits (no length is near 2^32)
+            nbs[i] = (int)(((unsigned)max(Ls[i], 0) + kBlockSize - 1) / kBlockSize);
+            const int full = is_cut(raw) ? (int)row_tokens : raw;
+            maxb = max(maxb, (int)(((unsigned)max(full, 0) + kBlockSize - 1) / kBlockSize));
             nonempty += __popcll(__ballot(nbs[i] > 0));
             cost += nbs[i] > 0 ? (unsigned)(nbs[i] + K) : 0u;
-            if (in) s_lens[r] = Ls[i];
+            if (lane * R < B) s_lens[lane * R + i] = Ls[i];   // (past B: never read, inside the array)
         }
         const unsigned hi = (unsigned)wave_incl_sum((int)cost), lo = hi - cost;
         const unsigned total = (unsigned)lane_value((int)hi, 63);
         const int longest = lane_value(wave_incl_max(maxb), 63);
-        if (stride == 0) stride = longest;
+        r.stride = p.bt_stride > 0 ? p.bt_stride : longest;
         nonempty = uniform(nonempty);
-        all_nonempty = nonempty == B;
+        r.all_nonempty = nonempty == B;
         const uint64_t V64 = (uint64_t)total * (unsigned)p.Hkv;
-        if ((V64 >> 32) != 0 || V64 * ((unsigned)p.launched + 1ull) > 0xffffffffull) return false;
+        if ((V64 >> 32) != 0 || V64 * ((unsigned)p.launched + 1ull) > 0xffffffffull) return r;
+        r.planned = true;
         const unsigned hk = (unsigned)p.Hkv, V32 = (unsigned)V64;
         const unsigned units = V32 - (unsigned)K * (unsigned)nonempty * hk;
         // a small batch of the default grid is cut by pairs (plan_policy.h): one
         // segment per work group
-        const unsigned floor_units = p.cus > 0 ? pair_cut_floor(units, (uint32_t)nonempty * hk, (uint32_t)longest,
-                                                                (uint32_t)p.cus, (uint32_t)p.launched)
-                                               : 0;
+        const unsigned floor_units = p.cus > 0 && 64 * R <= kPairCutRequests
+                                         ? pair_cut_floor(units, (uint32_t)nonempty * hk, (uint32_t)longest,
+                                                          (uint32_t)p.cus, (uint32_t)p.launched)
+                                         : 0;
         if (floor_units > 0) {
             unsigned T[R], parts[R], sum = 0;
 #pragma unroll
@@ -976,13 +1077,13 @@ __global__ __launch_bounds__(kAttnThreads) __attribute__((amdgpu_waves_per_eu(2)
             for (int i = 0; i < R; ++i) sum += parts[i];
             const unsigned phi = (unsigned)wave_incl_sum((int)sum), plo = phi - sum;
             const uint64_t hit = __ballot(plo * hk <= (unsigned)w && (unsigned)w < phi * hk);
-            if (hit == 0) return true;   // no part is left for this work group
+            if (hit == 0) return r;   // no part is left for this work group
             const int ln = __builtin_ctzll(hit);
             unsigned rest = (unsigned)w - (unsigned)lane_value((int)plo, ln) * hk;
             unsigned c = (unsigned)lane_value((int)parts[0], ln);
             int nb = lane_value(nbs[0], ln), per = lane_value((int)T[0], ln);
-            L = lane_value(Ls[0], ln);
-            b = ln * run;
+            r.L = lane_value(Ls[0], ln);
+            r.b = ln * R;
 #pragma unroll
             for (int i = 1; i < R; ++i) {
                 if (rest >= c * hk) {
@@ -990,59 +1091,78 @@ __global__ __launch_bounds__(kAttnThreads) __attribute__((amdgpu_waves_per_eu(2)
                     c = (unsigned)lane_value((int)parts[i], ln);
                     nb = lane_value(nbs[i], ln);
                     per = lane_value((int)T[i], ln);
-                    L = lane_value(Ls[i], ln);
-                    ++b;
+                    r.L = lane_value(Ls[i], ln);
+                    ++r.b;
                 }
             }
-            g = hk <= 64 ? __popcll(__ballot((unsigned)lane < hk && (unsigned)lane * c <= rest)) - 1
+            r.g = hk <= 64 ? __popcll(__ballot((unsigned)lane < hk && (unsigned)lane * c <= rest)) - 1
                          : uniform((int)(rest / c));
-            const int part = (int)rest - g * (int)c;
-            blk = part * per;
-            part_units = min(per, nb - blk);
-            cut_first = (int)w - part;
-            cut_last = cut_first + (int)c - 1;
-            v1 = 1;   // the group has work
-            return true;
+            const int part = (int)rest - r.g * (int)c;
+            r.blk = part * per;
+            r.part_units = min(per, nb - r.blk);
+            r.cut_first = (int)w - part;
+            r.cut_last = r.cut_first + (int)c - 1;
+            r.v1 = 1;   // the group has work
+            return r;
+        }
+        if (p.cus > 0 && waves_take_pairs(units, (uint32_t)nonempty * hk, (uint32_t)longest, (uint32_t)p.launched)) {
+            int mine = 0;
+#pragma unroll
+            for (int i = 0; i < R; ++i) mine += nbs[i] > 0;
+            int at = wave_incl_sum(mine) - mine;
+#pragma unroll
+            for (int i = 0; i < R; ++i)
+                if (nbs[i] > 0) s_order[at++] = lane * R + i;
+            r.short_pairs = nonempty * (int)hk;
+            return r;
         }
         const unsigned W32 = clamp_workers<uint32_t>(units >> __builtin_ctz((unsigned)p.min_units), units,
                                                      (uint32_t)p.launched, (uint32_t)nonempty * hk, (uint32_t)p.cus);
-        V = V32;
-        W = W32;
-        if (units == 0 || (unsigned)w >= W32) return true;
+        r.V = V32;
+        r.W = W32;
+        if (units == 0 || (unsigned)w >= W32) return r;
         const unsigned ends = ((unsigned)w + (lane & 1)) * V32 / W32;   // lane 0: start, lane 1: end
         const unsigned u0 = (unsigned)lane_value((int)ends, 0);
-        v0 = u0;
-        v1 = (unsigned)lane_value((int)ends, 1);
+        r.v0 = u0;
+        r.v1 = (unsigned)lane_value((int)ends, 1);
         // the lane whose requests hold u0, the request, the pair
         const int ln = __builtin_ctzll(__ballot(lo * hk <= u0 && u0 < hi * hk));
         unsigned vpre = (unsigned)lane_value((int)lo, ln) * hk;
         int nb = lane_value(nbs[0], ln);
-        L = lane_value(Ls[0], ln);
-        b = ln * run;
+        r.L = lane_value(Ls[0], ln);
+        r.b = ln * R;
 #pragma unroll
         for (int i = 1; i < R; ++i) {
             const unsigned span = nb > 0 ? (unsigned)(nb + K) * hk : 0u;
             if (u0 >= vpre + span) {
                 vpre += span;
                 nb = lane_value(nbs[i], ln);
-                L = lane_value(Ls[i], ln);
-                ++b;
+                r.L = lane_value(Ls[i], ln);
+                ++r.b;
             }
         }
         const unsigned per = (unsigned)(nb + K);
         // kv-head: pair g of the request starts at vpre + g per
-        g = hk <= 64 ? __popcll(__ballot((unsigned)lane < hk && vpre + (unsigned)lane * per <= u0)) - 1
+        r.g = hk <= 64 ? __popcll(__ballot((unsigned)lane < hk && vpre + (unsigned)lane * per <= u0)) - 1
                      : uniform((int)((u0 - vpre) / per));
-        const unsigned first = vpre + (unsigned)g * per + (unsigned)K;   // position of the pair's block 0
-        vf = first;
-        blk = u0 > first ? (int)(u0 - first) : 0;
-        return true;
+        const unsigned first = vpre + (unsigned)r.g * per + (unsigned)K;   // position of the pair's block 0
+        r.vf = first;
+        r.blk = u0 > first ? (int)(u0 - first) : 0;
+        return r;
     };
-    bool planned = false;
+    WavePlan plan;
     if (B <= 64)
-        planned = plan_in_wave(std::integral_constant<int, 1>());
-    else if (B <= kPairCutRequests)
-        planned = plan_in_wave(std::integral_constant<int, 4>());
+        plan = plan_in_wave(std::integral_constant<int, 1>());
+    else if (B <= 256)
+        plan = plan_in_wave(std::integral_constant<int, 4>());
+    else if (B <= kShortRequests)
+        plan = plan_in_wave(std::integral_constant<int, 8>());
+
+    const int short_pairs = plan.short_pairs, part_units = plan.part_units;
+    const int cut_first = plan.cut_first, cut_last = plan.cut_last;
+    bool all_nonempty = plan.all_nonempty;
+    int b = plan.b, g = plan.g, blk = plan.blk, L = plan.L;
+    int64_t V = plan.V, W = plan.W, v0 = plan.v0, v1 = plan.v1, vf = plan.vf, stride = plan.stride;
 
     // Larger batches (and partitions past 32 bits): context_lens is read once
     // by the group, each thread sums the blocks of a contiguous run of
@@ -1050,7 +1170,7 @@ __global__ __launch_bounds__(kAttnThreads) __attribute__((amdgpu_waves_per_eu(2)
     // plus one barrier give the prefix sums, the total, the longest request
     // and the non-empty requests.  Redundant per-wave runs of more than four
     // requests would cost more than the barriers they save.
-    if (!planned) {
+    if (!plan.planned) {
     const int seg = (B + kAttnThreads - 1) / kAttnThreads;
     const int r0 = min(B, tid * seg);
     const int r1 = min(B, r0 + seg);
@@ -1161,6 +1281,34 @@ __global__ __launch_bounds__(kAttnThreads) __attribute__((amdgpu_waves_per_eu(2)
     all_nonempty = uniform(nonempty) == B;
     }
 
+    if (short_pairs > 0) {
+        // every wave takes whole pairs of its own, launched * kWaves pairs
+        // apart: no barrier, no merge, the rows straight from its registers
+#ifdef APEX_TRACE_WORK_GROUPS
+        if (tid == 0) s_trace[1] = trace_clock();
+#endif
+        const int wv = uniform(wave);
+        for (int i = (int)w + wv * p.launched; i < short_pairs; i += p.launched * kWaves) {
+            const int k = uniform((int)((unsigned)i / (unsigned)p.Hkv));
+            const int bp = uniform(s_order[k]), Lp = uniform(s_lens[bp]);
+            const int32_t* row = bt + (size_t)bp * (size_t)stride;
+            const WaveSeg cs = wave_seg<G, 1>(p, row, bp, i - k * p.Hkv, 0, (int)blocks_of(Lp, kBlockSize), 0, lane);
+            WaveTiles st;
+            WaveState ws;
+            NewTokenElems<kEmitElems<G>> unused;
+            load_first_tiles<kCheck, 1>(p, cs, bt, st, lane);
+            load_q<G>(st.qnext, cs, lane);
+            wave_attend<G, kCheck, kAppend, 1>(p, cs, cs, bt, false, Lp, st, wave, lane, ws, s_new[wv], row, unused);
+            emit_wave<G, kCheck, kAppend>(p, ws, bp, cs.g, Lp + 1, lane, s_new[wv], row, bt);
+#ifdef APEX_TRACE_WORK_GROUPS
+            if (tid == 0) {
+                ++s_trace[4];
+                s_trace[6] += cs.n;
+            }
+#endif
+        }
+    }
+
     // A segment is the worker's blocks of one pair: from block blk of the pair
     // whose block 0 lies at position vf, up to the pair's end or the worker's
     // range end v1, whichever comes first (none when v1 falls on or before
@@ -1202,7 +1350,7 @@ __global__ __launch_bounds__(kAttnThreads) __attribute__((amdgpu_waves_per_eu(2)
 #ifdef APEX_TRACE_WORK_GROUPS
     if (tid == 0) s_trace[1] = trace_clock();
 #endif
-    WaveSeg cs = wave_seg<G>(p, bt + (size_t)uniform(b) * (size_t)stride, b, g, blk, blk + take, wave, lane);
+    WaveSeg cs = wave_seg<G, kWaves>(p, bt + (size_t)uniform(b) * (size_t)stride, b, g, blk, blk + take, wave, lane);
     WaveTiles st;
     st.prefetched = false;
     st.cur0 = st.cur1 = st.nid0 = st.nid1 = 0;
@@ -1212,13 +1360,13 @@ __global__ __launch_bounds__(kAttnThreads) __attribute__((amdgpu_waves_per_eu(2)
         int64_t vf2 = vf;
         // the loads of a segment that the pipeline did not run on into go out
         // before the next segment is looked up
-        if (!st.prefetched) load_first_tiles<kCheck>(p, cs, bt, st, lane);
+        if (!st.prefetched) load_first_tiles<kCheck, kWaves>(p, cs, bt, st, lane);
         const bool more = part_units == 0 && advance(b2, L2, nb2, g2, blk2, vf2, take);
         const int take2 = more ? seg_take(nb2, blk2, vf2) : 0;
         WaveSeg ns = cs;
         ns.n = 0;
         if (more)
-            ns = wave_seg<G>(p, bt + (size_t)uniform(b2) * (size_t)stride, b2, g2, blk2, blk2 + take2, wave,
+            ns = wave_seg<G, kWaves>(p, bt + (size_t)uniform(b2) * (size_t)stride, b2, g2, blk2, blk2 + take2, wave,
                              lane);
         // the pair's first and last work groups: this one, unless the range
         // cuts the pair (found here, while the loads are in flight)
@@ -1227,10 +1375,14 @@ __global__ __launch_bounds__(kAttnThreads) __attribute__((amdgpu_waves_per_eu(2)
                        : blk + take == nb ? (int)w
                                           : uniform((int)worker_of(vf + nb - 1, V, W));
         NewTokenElems<kEmitElems<G>> ne;
-        wave_attend<G, kCheck, kAppend>(p, cs, ns, bt,
-                                        more && take >= kPrefetchBlocks && take2 >= kPrefetchBlocks, L,
-                                        st, wave, lane, s_acc, s_m, s_l, s_new,
-                                        bt + (size_t)uniform(b) * (size_t)stride, ne);
+        {
+            WaveState ws;
+            wave_attend<G, kCheck, kAppend, kWaves>(p, cs, ns, bt,
+                                                    more && take >= kPrefetchBlocks && take2 >= kPrefetchBlocks, L,
+                                                    st, wave, lane, ws, s_new[0],
+                                                    bt + (size_t)uniform(b) * (size_t)stride, ne);
+            store_wave_state<G>(ws, wave, lane, s_acc, s_m, s_l);
+        }
         __syncthreads();
 #ifdef APEX_TRACE_WORK_GROUPS
         if (tid == 0) {
@@ -1246,7 +1398,7 @@ __global__ __launch_bounds__(kAttnThreads) __attribute__((amdgpu_waves_per_eu(2)
         const bool emits = G >= 2 || tid < D;
         auto emit = [&](RowState<N>& r) {
             if (append) {
-                fold_new_token<N>(s_new[h], ne.vn, r);
+                fold_new_token<N>(s_new[0][h], ne.vn, r);
                 if (h == 0) store_new_token<kCheck, N>(p, ne, g, L + 1, dim);
             }
             write_row<N>(p, b, g * G + h, dim, r);

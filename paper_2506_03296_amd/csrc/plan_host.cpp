@@ -76,9 +76,15 @@ int apex_decode_plan_pairs_host(const int32_t* context_lens, int B, int Hq, int 
     const uint64_t units = blocks * (uint64_t)Hkv, pairs = nonempty * (uint64_t)Hkv;
     const uint64_t V = units + apex::kSegmentCostUnits * pairs;
     uint32_t floor_units = 0;
-    if (B <= apex::kPairCutRequests && cus > 0 && (V >> 32) == 0 && V * ((uint64_t)launched_workers + 1) <= 0xffffffffull)
-        floor_units = apex::pair_cut_floor((uint32_t)units, (uint32_t)pairs, (uint32_t)longest, (uint32_t)cus,
-                                           (uint32_t)launched_workers);
+    bool by_waves = false;
+    if (cus > 0 && (V >> 32) == 0 && V * ((uint64_t)launched_workers + 1) <= 0xffffffffull) {
+        if (B <= apex::kPairCutRequests)
+            floor_units = apex::pair_cut_floor((uint32_t)units, (uint32_t)pairs, (uint32_t)longest, (uint32_t)cus,
+                                               (uint32_t)launched_workers);
+        by_waves = B <= apex::kShortRequests && floor_units == 0 &&
+                   apex::waves_take_pairs((uint32_t)units, (uint32_t)pairs, (uint32_t)longest, (uint32_t)launched_workers);
+    }
+    if (by_waves) floor_units = (uint32_t)longest;   // every pair is one part
     int64_t active = 0;
     for (int b = 0; b < B; ++b) {
         const uint32_t nb = (uint32_t)apex::blocks_of(context_lens[b], block_size);
@@ -91,6 +97,7 @@ int apex_decode_plan_pairs_host(const int32_t* context_lens, int B, int Hq, int 
         if (parts_out) parts_out[b] = (int32_t)parts;
         if (part_units_out) part_units_out[b] = (int32_t)T;
     }
+    if (by_waves) active = launched_workers;   // pairs > launched_workers
     if (active_out) *active_out = active;
     return APEX_OK;
 }

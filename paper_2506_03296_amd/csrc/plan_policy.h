@@ -154,4 +154,24 @@ __host__ __device__ inline uint32_t pair_part_units(uint32_t nb, uint32_t floor_
     return T > floor_units ? T : floor_units;
 }
 
+// Short pairs: with more pairs than work groups, a group attends several one
+// after the other, and a pair of a few blocks costs it a first-tile latency, a
+// join and a merge (7 us and half a microsecond a block on the line) for one or
+// two blocks per wave.  Instead every wave takes whole pairs of its own: 3 us
+// and 1.2 us a block for the longest, all waves at once, no barrier, no merge.
+// Kernel time, line -> waves: 2048 pairs of 20-60 tokens 21.2 -> 11.5 us, 2400
+// of 16-48 22.6 -> 13.2, 1280 of 16-130 (G = 8) 21.9 -> 13.2, 2048 of 200-256
+// 46.3 -> 38.7.  The rule compares the two estimates; it keeps 640 pairs of
+// 200-256 on the line (20.9 us, 27.2 by waves).  Past 32 blocks the streaming
+// hides the line's cost and whole pairs only balance worse (2048 pairs of
+// 512-2048 tokens 204.6 on the line, 220.6 by waves).
+constexpr int kShortRequests = 512;   // the kernel's in-register partition, eight requests per lane
+constexpr uint32_t kShortPairUnits = 32;
+
+__host__ __device__ inline bool waves_take_pairs(uint32_t units, uint32_t pairs, uint32_t longest, uint32_t launched)
+{
+    return pairs > launched && longest <= kShortPairUnits &&
+           (30 + 12 * longest) * (uint64_t)launched <= 70 * (uint64_t)pairs + 5 * (uint64_t)units;
+}
+
 }  // namespace apex

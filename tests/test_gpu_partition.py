@@ -1,16 +1,17 @@
 """The partition of the attention kernel at the edges of its forms, the pair
-cut of small batches, and the combine of split pairs.
+cut of small batches, whole pairs per wave, and the combine of split pairs.
 
-Batches of up to 256 requests are partitioned by every wave in registers (one
-request per lane up to 64, four above), larger ones and partitions past 32 bits
-by the work group through LDS.  All give the same ranges, so a batch padded
+Batches of up to 512 requests are partitioned by every wave in registers (one
+request per lane up to 64, four up to 256, eight above), larger ones and
+partitions past 32 bits by the work group through LDS.  All give the same ranges, so a batch padded
 with empty requests from one form into the next must give the same bits.
 """
 import numpy as np
 import pytest
 
 import apex_workloads as W
-from test_gpu_parity import apex, assert_parity, run_gpu, torch_cuda  # noqa: F401  (fixtures)
+from test_gpu_parity import (FP32_ALLOWANCE, apex, assert_parity, fp16_ulp, run_gpu,  # noqa: F401  (fixtures)
+                             torch_cuda)
 
 pytestmark = pytest.mark.gpu
 
@@ -24,7 +25,7 @@ def ragged(B, seed):
 
 
 @pytest.mark.parametrize("Hq,Hkv", [(8, 1), (16, 8), (65, 65)], ids=["one_head", "g2", "65_heads"])
-@pytest.mark.parametrize("B", [1, 63, 64, 65, 129, 256, 257])
+@pytest.mark.parametrize("B", [1, 63, 64, 65, 129, 256, 257, 511])
 def test_partition_forms_agree(torch_cuda, apex, oracle_mod, B, Hq, Hkv):  # noqa: F811
     lens = ragged(B, seed=B)
     case = W.make_host_case(lens, Hq, Hkv, seed=B + Hq, poison=True)
@@ -34,7 +35,7 @@ def test_partition_forms_agree(torch_cuda, apex, oracle_mod, B, Hq, Hkv):  # noq
         got = run_gpu(torch_cuda, apex, case, num_workers=workers)
         assert_parity(got, ref, f"B={B} heads {Hq}/{Hkv} workers={workers}")
         assert np.all(got[np.asarray(lens) == 0] == 0)
-        for pad_to in (65, 257):
+        for pad_to in (65, 257, 513):
             if pad_to <= B:
                 continue
             n = pad_to - B
@@ -43,8 +44,8 @@ def test_partition_forms_agree(torch_cuda, apex, oracle_mod, B, Hq, Hkv):  # noq
                                 case.v_cache, table,
                                 np.concatenate([case.context_lens, np.zeros(n, np.int32)]), case.scale)
             more = run_gpu(torch_cuda, apex, padded, num_workers=workers)
-            # (the default grid cuts a small batch of up to 256 requests by
-            # pairs and never a larger one: not the same ranges)
+            # (the default grid partitions some batches by pairs, up to 256
+            # and 512 requests: not the same ranges)
             if workers or apex.plan_pairs_host(lens, Hq, Hkv, 512, 256)["active"] == 0:
                 assert np.array_equal(more[:B].view(np.uint16), got.view(np.uint16)), f"padded to {pad_to}"
             assert_parity(more[:B], ref, f"padded to {pad_to}")
@@ -81,7 +82,7 @@ PAIR_CUTS = [
     ("257_pairs", [300] * 257, 1, 1, False),
     ("258_pairs", [40, 300] * 64 + [16], 8, 2, True),
     ("512_pairs", [100, 7] * 32, 8, 8, True),
-    ("520_pairs", [100, 7] * 32 + [9], 8, 8, False),
+    ("520_pairs", [300, 7] * 32 + [9], 8, 8, False),
     ("100_requests", list(range(1, 401, 4)), 16, 2, True),
     ("65_heads", [700, 40], 65, 65, True),
     ("long_pair", [60000], 8, 1, True),
@@ -104,3 +105,90 @@ def test_pair_cut(torch_cuda, apex, oracle_mod, name, lens, Hq, Hkv, cut):  # no
         assert_parity(got, ref, f"{name} {kw}")
         assert np.all(got[np.asarray(lens) == 0] == 0)
     assert apex.check_device_error() == 0
+
+
+# (lens, Hq, Hkv): pairs around one per work group (512) and one per wave
+# (2048), one and eight requests per lane, blocks up to the largest (32), block
+# edges, empty requests and requests whose only token is the current one
+SHORT = [
+    ("513_pairs", [1, 16, 17] * 57, 12, 3),
+    ("520_pairs_65", [100, 7, 1] * 21 + [9, 0], 8, 8),
+    ("2048_pairs", [33, 5, 60, 128] * 64, 16, 8),
+    ("2056_pairs", [20, 1, 16, 30] * 64 + [48], 64, 8),
+    ("ragged_32_blocks", [int(x) for x in np.random.default_rng(3).integers(0, 513, size=300)], 32, 32),
+    ("512_requests", [int(x) for x in np.random.default_rng(4).integers(0, 90, size=512)], 32, 16),
+]
+
+
+@pytest.mark.parametrize("name,lens,Hq,Hkv", SHORT, ids=[c[0] for c in SHORT])
+def test_short_pairs_per_wave(torch_cuda, apex, oracle_mod, name, lens, Hq, Hkv):  # noqa: F811
+    torch = torch_cuda
+    plan = apex.plan_pairs_host(lens, Hq, Hkv, 512, 256)
+    assert plan["active"] == 512 and plan["parts"].max() == 1
+    case = W.make_host_case(lens, Hq, Hkv, seed=len(lens) + Hq, poison=True)
+    ref, lse_ref = oracle_mod.decode_attention_f64(case.q, case.k_cache, case.v_cache, case.block_table,
+                                                   case.context_lens, case.scale, return_lse=True)
+    empty = np.asarray(lens) == 0
+    for kw in ({}, dict(check_inputs=True)):
+        lse = torch.zeros((len(lens), Hq), dtype=torch.float32, device="cuda")
+        got = run_gpu(torch_cuda, apex, case, lse_out=lse, **kw)
+        assert_parity(got, ref, f"{name} {kw}")
+        lse = lse.cpu().numpy()
+        assert np.all(got[empty] == 0) and np.all(np.isneginf(lse[empty]))
+        # fp32 sums of at most 513 weights and one logarithm
+        assert np.abs(lse[~empty] - lse_ref[~empty]).max() <= 1e-5
+    assert apex.check_device_error() == 0
+    # every output is an fp16 neighbour of the exact value, up to fp32 rounding
+    assert np.all(np.abs(got[~empty].astype(np.float64) - ref[~empty]) <= fp16_ulp(ref[~empty]) + FP32_ALLOWANCE)
+
+
+@pytest.mark.parametrize("name,lens,Hq,Hkv", SHORT[:4], ids=[c[0] for c in SHORT[:4]])
+@pytest.mark.parametrize("check", [False, True])
+def test_short_pairs_with_the_fused_append(torch_cuda, apex, oracle_mod, name, lens, Hq, Hkv, check):  # noqa: F811
+    """The fused append equals the append followed by the plain call: outputs
+    to the bar, caches bit for bit (the current slots hold NaN before)."""
+    torch = torch_cuda
+    lens = [L + 1 if L else 0 for L in lens]
+    case = W.make_host_case(lens, Hq, Hkv, seed=7 + len(lens), poison=True)
+    rng = np.random.default_rng(8)
+    kn, vn = (rng.standard_normal((len(lens), Hkv, 128)).astype(np.float16) for _ in range(2))
+    k, v = case.k_cache.copy(), case.v_cache.copy()
+    k0, v0 = k.copy(), v.copy()
+    for b, L in enumerate(lens):
+        if L:
+            blk, pos = case.block_table[b, (L - 1) // 16], (L - 1) % 16
+            k[blk, :, pos], v[blk, :, pos] = kn[b], vn[b]
+            k0[blk, :, pos] = v0[blk, :, pos] = np.nan
+    ref = oracle_mod.decode_attention_f64(case.q, k, v, case.block_table, case.context_lens, case.scale)
+    dev = [torch.from_numpy(x).cuda() for x in (case.q, k0, v0, case.block_table, case.context_lens, kn, vn)]
+    got = apex.decode_attention_ex(*dev[:5], case.scale, k_new=dev[5], v_new=dev[6], check_inputs=check)
+    assert_parity(got.cpu().numpy(), ref, f"{name} fused, check={check}")
+    assert np.array_equal(dev[1].cpu().numpy().view(np.uint16), k.view(np.uint16))
+    assert np.array_equal(dev[2].cpu().numpy().view(np.uint16), v.view(np.uint16))
+    assert not check or apex.check_device_error() == 0
+
+
+def test_short_pairs_skip_block_ids_outside_the_pool(torch_cuda, apex, oracle_mod):  # noqa: F811
+    """A bad id leaves out its block's tokens: the first, a middle, the last
+    block of a pair, and a pair that has no other."""
+    lens = [40, 16, 64, 33] * 128
+    case = W.make_host_case(lens, 2, 2, seed=11, poison=False)
+    assert apex.plan_pairs_host(lens, 2, 2, 512, 256)["active"] == 512
+    bad = {0: 0, 1: 0, 2: 2, 3: 2, 511: 1, 262: 0}
+    keep = case.block_table.copy()
+    for b, i in bad.items():
+        case.block_table[b, i] = -5 if b % 2 else case.k_cache.shape[0]
+    got = run_gpu(torch_cuda, apex, case, check_inputs=True)
+    assert apex.check_device_error() == apex.DEVICE_ERR_BLOCK_ID
+    case.block_table[:] = keep
+    for b, L in enumerate(lens):
+        tok = np.arange(L)
+        if b in bad:
+            tok = tok[tok // 16 != bad[b]]
+        ids = keep[b, tok // 16]
+        kk, vv = (c[ids, :, tok % 16].astype(np.float64) for c in (case.k_cache, case.v_cache))
+        for h in range(2):
+            s = kk[:, h] @ case.q[b, h].astype(np.float64) * float(case.scale)
+            w = np.exp(s - s.max()) if len(s) else s
+            want = (w[:, None] * vv[:, h]).sum(0) / w.sum() if len(s) else np.zeros(128)
+            assert np.abs(got[b, h] - want).max() <= 2e-3, (b, h)

@@ -1,5 +1,5 @@
-"""Host mirror of the pair cut of small batches (no GPU): every pair's parts
-cover it, fit the work groups and keep to the largest part."""
+"""Host mirror of the partitions by pairs (no GPU): every pair's parts cover it,
+fit the work groups and keep to the largest part; short pairs stay whole."""
 import numpy as np
 import pytest
 
@@ -9,9 +9,9 @@ import paper_2506_03296_amd as A
 @pytest.mark.parametrize("seed", range(8))
 def test_parts_cover_every_pair_and_fit_the_work_groups(seed):
     rng = np.random.default_rng(seed)
-    applied = 0
+    applied = whole = 0
     for _ in range(300):
-        B = int(np.exp(rng.uniform(0, np.log(300))))
+        B = int(np.exp(rng.uniform(0, np.log(600))))
         hi = int(np.exp(rng.uniform(np.log(2), np.log(20000))))
         lens = rng.integers(-1, hi, size=B)
         Hkv = int(rng.choice([1, 2, 8, 16, 32, 80]))
@@ -22,7 +22,14 @@ def test_parts_cover_every_pair_and_fit_the_work_groups(seed):
         pairs, units, longest = int((blocks > 0).sum()) * Hkv, int(blocks.sum()) * Hkv, int(blocks.max())
         groups = min(cus, launched) if pairs <= cus else launched
         fits = cus > 0 and B <= 256 and 0 < pairs <= groups and (longest <= 32 or units <= 32 * (groups - pairs))
-        assert (p["active"] > 0) == fits
+        short = (cus > 0 and not fits and B <= 512 and pairs > launched and longest <= 32
+                 and (30 + 12 * longest) * launched <= 70 * pairs + 5 * units)
+        assert (p["active"] > 0) == (fits or short)
+        if short:
+            whole += 1
+            assert p["active"] == launched
+            assert np.array_equal(p["parts"], blocks > 0) and np.array_equal(p["part_units"], blocks)
+            continue
         if not fits:
             assert not p["parts"].any()
             continue
@@ -34,7 +41,7 @@ def test_parts_cover_every_pair_and_fit_the_work_groups(seed):
         assert np.all((parts[used] - 1) * T[used] < blocks[used])      # no empty part
         assert np.all(parts[used] * T[used] >= blocks[used])           # nothing left over
         assert np.all(parts[blocks <= 16] <= 1)
-    assert applied > 20
+    assert applied > 20 and whole > 5
 
 
 def test_bad_arguments_are_refused():
