@@ -1041,6 +1041,8 @@ __global__ __launch_bounds__(kAttnThreads) __attribute__((amdgpu_waves_per_eu(2)
             cost += nbs[i] > 0 ? (unsigned)(nbs[i] + K) : 0u;
             if (lane * R < B) s_lens[lane * R + i] = Ls[i];   // (past B: never read, inside the array)
         }
+        // every wave writes the same values and reads back what it wrote
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
         const unsigned hi = (unsigned)wave_incl_sum((int)cost), lo = hi - cost;
         const unsigned total = (unsigned)lane_value((int)hi, 63);
         const int longest = lane_value(wave_incl_max(maxb), 63);
@@ -1113,6 +1115,7 @@ __global__ __launch_bounds__(kAttnThreads) __attribute__((amdgpu_waves_per_eu(2)
 #pragma unroll
             for (int i = 0; i < R; ++i)
                 if (nbs[i] > 0) s_order[at++] = lane * R + i;
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
             r.short_pairs = nonempty * (int)hk;
             return r;
         }
