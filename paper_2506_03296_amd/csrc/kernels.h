@@ -40,6 +40,7 @@
 #pragma once
 
 #include <hip/hip_runtime.h>
+#include <float.h>
 #include <stdint.h>
 
 #include <type_traits>
@@ -700,7 +701,9 @@ __device__ inline void emit_wave(const AttnParams& p, WaveState& ws, int b, int 
         const int head = g * G + col;
         f16* row = p.out + ((size_t)b * p.Hq + head) * kHeadDim + 32 * q;
         // one reciprocal per head; a quotient with one correction step is
-        // within half an ulp and a rounding of the division's
+        // within half an ulp and a rounding of the division's.  An infinite
+        // numerator (an infinite V value) has no remainder (inf - inf): the
+        // maximum turns that NaN into a number and the quotient stays infinite.
         const float inv = den > 0.f ? 1.f / den : 0.f;
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
@@ -708,7 +711,7 @@ __device__ inline void emit_wave(const AttnParams& p, WaveState& ws, int b, int 
 #pragma unroll
             for (int t = 0; t < 8; ++t) {
                 const float a = ws.acc[t][i], y = a * inv;
-                const float z = fmaf(fmaf(-y, den, a), inv, y);
+                const float z = fmaf(fmaxf(fmaf(-y, den, a), -FLT_MAX), inv, y);
                 o[t] = (f16)(den > 0.f ? z : 0.f);
             }
             *(f16x8*)(row + 8 * i) = o;

@@ -192,3 +192,23 @@ def test_short_pairs_skip_block_ids_outside_the_pool(torch_cuda, apex, oracle_mo
             w = np.exp(s - s.max()) if len(s) else s
             want = (w[:, None] * vv[:, h]).sum(0) / w.sum() if len(s) else np.zeros(128)
             assert np.abs(got[b, h] - want).max() <= 2e-3, (b, h)
+
+
+@pytest.mark.parametrize("Hq,Hkv", [(4, 4), (16, 2)])
+def test_short_pairs_keep_infinite_values(torch_cuda, apex, Hq, Hkv):  # noqa: F811
+    """An infinite value in the current token's V row (its weight is positive)
+    gives that infinity in its dim, as the cost line does; the other dims stay finite."""
+    torch = torch_cuda
+    lens = [17, 33, 20, 50] * (1024 // (4 * Hkv))
+    assert apex.plan_pairs_host([L - 1 for L in lens], Hq, Hkv, 512, 256)["active"] == 512
+    case = W.make_host_case(lens, Hq, Hkv, seed=5, poison=False)
+    rng = np.random.default_rng(9)
+    kn, vn = (rng.standard_normal((len(lens), Hkv, 128)).astype(np.float16) for _ in range(2))
+    vn[0, 0, 0], vn[7, -1, 127], vn[-1, 0, 64] = np.inf, -np.inf, np.inf
+    want = np.repeat(np.where(np.isinf(vn), vn, np.float16(0)), Hq // Hkv, axis=1)
+    for kw in ({}, dict(num_workers=512)):   # pairs by waves; an explicit grid is cut on the line
+        dev = [torch.from_numpy(x).cuda() for x in (case.q, case.k_cache, case.v_cache, case.block_table,
+                                                    case.context_lens, kn, vn)]
+        got = apex.decode_attention_ex(*dev[:5], case.scale, k_new=dev[5], v_new=dev[6], **kw).cpu().numpy()
+        assert not np.isnan(got).any(), kw
+        assert np.array_equal(np.where(np.isinf(got), got, np.float16(0)), want), kw
