@@ -219,14 +219,6 @@ __device__ inline T* uniform_ptr(T* p)
     return (T*)uniform64((int64_t)p);
 }
 
-// Device-scope coherent accesses (relaxed atomics at agent scope).  On gfx950
-// they carry the sc1 cache-coherence bit, so work groups on different XCDs
-// (each with its own L2) see each other's values without any cache flush.
-__device__ inline void store_coherent(float* p, float v)
-{
-    __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-
 typedef _Float16 f16x4 __attribute__((ext_vector_type(4)));
 typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
@@ -248,9 +240,10 @@ constexpr int kRawBufferWord3 = 0x00020000;
 // Cache policy of the K/V loads: non-temporal (bit 1) -- each row is read
 // exactly once per call, so it should not displace reusable lines.
 constexpr int kStreamingLoad = 2;
-// Cache policy of a wide device-coherent load (sc1), the counterpart of
-// store_coherent.
-constexpr int kCoherentLoad = 16;
+// Cache policy of device-coherent accesses (sc1, the bit of relaxed atomics at
+// agent scope): work groups on different XCDs, each with its own L2, see each
+// other's values without any cache flush.
+constexpr int kCoherent = 16;
 
 // Operand layouts of one slab (lane = 16 q + c, q = lane / 16, c = lane % 16):
 //   K: word i of lane (c, q) = token c, dims [32i + 8q, +8)   (A of S^T = K Q^T)
@@ -817,6 +810,44 @@ struct Partials {
 };
 
 
+__device__ inline void store_coherent(float* p, float v)
+{
+    __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// Stores elements [e0, e0 + N) of a work group's partial (all of head h; with
+// `first` also the head's max and sum), device-coherent.  A coherent store goes
+// through to memory by itself, so with N > 1 (G = 4 and 8) single words wrote
+// every line N times, and one vector store does it once: 48 requests of
+// 512-8192 tokens, G = 4, 22.7 -> 22.4 us, 12 of 2048-16384, G = 8, 79.1 ->
+// 78.4.  With N = 1 (G = 1 and 2) the plain store needs no resource: 4 requests
+// of 17-511 tokens 8.72 us, 8.97 through one.
+template <int G, int N>
+__device__ inline void store_partial(const AttnParams& p, int64_t slot, int e0, int h, bool first,
+                                     const RowState<N>& r)
+{
+    if constexpr (N == 1) {
+        store_coherent(&p.pacc[slot * (G * kHeadDim) + e0], r.num[0]);
+        if (first) {
+            store_coherent(&p.pml[((size_t)slot * G + h) * 2 + 0], r.M);
+            store_coherent(&p.pml[((size_t)slot * G + h) * 2 + 1], r.den);
+        }
+    } else {
+        const auto acc = __builtin_amdgcn_make_buffer_rsrc((void*)uniform_ptr(p.pacc + slot * (G * kHeadDim)),
+                                                           (short)0, Partials<G>::kRow, kRawBufferWord3);
+        if constexpr (N == 2)
+            __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, r.num), acc, e0 * 4, 0, kCoherent);
+        else
+            __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, r.num), acc, e0 * 4, 0, kCoherent);
+        if (first) {
+            const auto ml = __builtin_amdgcn_make_buffer_rsrc((void*)uniform_ptr(p.pml + slot * (G * 2)), (short)0,
+                                                              Partials<G>::kMl, kRawBufferWord3);
+            const u32x2 v = {__float_as_uint(r.M), __float_as_uint(r.den)};
+            __builtin_amdgcn_raw_buffer_store_b64(v, ml, h * 8, 0, kCoherent);
+        }
+    }
+}
+
 // Rescales r to the running max of C more (max, sum) pairs and adds their
 // sums; cf gets the contributors' factors.
 template <int N, int C>
@@ -853,14 +884,14 @@ __device__ inline void combine_few(const AttnParams& p, int wf, int nc, int e0, 
     f32xN a[C];
 #pragma unroll
     for (int j = 0; j < C; ++j) {
-        ml[j] = __builtin_amdgcn_raw_buffer_load_b64(ps.ml, h * 8 + ps.slot(j) * ps.kMl, 0, kCoherentLoad);
+        ml[j] = __builtin_amdgcn_raw_buffer_load_b64(ps.ml, h * 8 + ps.slot(j) * ps.kMl, 0, kCoherent);
         const int off = e0 * 4 + ps.slot(j) * ps.kRow;
         if constexpr (N == 1)
-            a[j] = __builtin_bit_cast(f32xN, __builtin_amdgcn_raw_buffer_load_b32(ps.acc, off, 0, kCoherentLoad));
+            a[j] = __builtin_bit_cast(f32xN, __builtin_amdgcn_raw_buffer_load_b32(ps.acc, off, 0, kCoherent));
         else if constexpr (N == 2)
-            a[j] = __builtin_bit_cast(f32xN, __builtin_amdgcn_raw_buffer_load_b64(ps.acc, off, 0, kCoherentLoad));
+            a[j] = __builtin_bit_cast(f32xN, __builtin_amdgcn_raw_buffer_load_b64(ps.acc, off, 0, kCoherent));
         else
-            a[j] = __builtin_bit_cast(f32xN, __builtin_amdgcn_raw_buffer_load_b128(ps.acc, off, 0, kCoherentLoad));
+            a[j] = __builtin_bit_cast(f32xN, __builtin_amdgcn_raw_buffer_load_b128(ps.acc, off, 0, kCoherent));
     }
     float cf[C];
     fold_sums<N, C>(ml, nc, r, cf);
@@ -876,7 +907,7 @@ __device__ inline void load_to_lds(__amdgpu_buffer_rsrc_t r, float* dst, int off
 {
 #ifdef __HIP_DEVICE_COMPILE__
     __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (__attribute__((address_space(3))) void*)dst, 16, off, 0, 0,
-                                             kCoherentLoad);
+                                             kCoherent);
 #endif
 }
 
@@ -911,7 +942,7 @@ __device__ inline void combine_wave(const AttnParams& p, int wf, int c0, int c1,
         u32x2 ml[C];
 #pragma unroll
         for (int j = 0; j < C; ++j) {
-            ml[j] = __builtin_amdgcn_raw_buffer_load_b64(ps.ml, h * 8 + ps.slot(j) * ps.kMl, 0, kCoherentLoad);
+            ml[j] = __builtin_amdgcn_raw_buffer_load_b64(ps.ml, h * 8 + ps.slot(j) * ps.kMl, 0, kCoherent);
             if (j < n) {
 #pragma unroll
                 for (int k = 0; k < kLoads; ++k)
@@ -1420,12 +1451,7 @@ __global__ __launch_bounds__(kAttnThreads) __attribute__((amdgpu_waves_per_eu(2)
             if (wf == wl) {
                 emit(r);
             } else {
-#pragma unroll
-                for (int i = 0; i < N; ++i) store_coherent(&p.pacc[((size_t)slot * G + h) * D + dim + i], r.num[i]);
-                if (dim == 0) {
-                    store_coherent(&p.pml[((size_t)slot * G + h) * 2 + 0], r.M);
-                    store_coherent(&p.pml[((size_t)slot * G + h) * 2 + 1], r.den);
-                }
+                store_partial<G, N>(p, slot, tid * N, h, dim == 0, r);
             }
         }
         if (wf != wl) {
@@ -1436,6 +1462,7 @@ __global__ __launch_bounds__(kAttnThreads) __attribute__((amdgpu_waves_per_eu(2)
             // them to complete before the arrival is counted makes them visible
             // to the last arriver's device-coherent loads, on whichever XCD it
             // runs, without writing back or invalidating the L2.
+            asm volatile("" ::: "memory");   // (no store moves past the wait)
             __builtin_amdgcn_s_waitcnt(0);
             __syncthreads();
             if (tid == 0) {
