@@ -668,6 +668,11 @@ __device__ inline void emit_wave(const AttnParams& p, WaveState& ws, int b, int 
         f16x8 v[4];
 #pragma unroll
         for (int i = 0; i < 4; ++i) v[i] = *(const f16x8*)(p.v_new + src + 32 * q + 8 * i);
+        // lane 63 has just written the logits that all lanes read.  Without the
+        // fence a lane's own view allows the read first: for G = 1, where both
+        // are one address, the compiler read the previous pair's logit in the
+        // lanes that do not write
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
         const float sn = s_new[col < G ? col : 0];
         const float M2 = fmaxf(M, sn);
         const float f = M == -INFINITY ? 0.f : exp2_fast(M - M2);

@@ -107,14 +107,26 @@ def test_pair_cut(torch_cuda, apex, oracle_mod, name, lens, Hq, Hkv, cut):  # no
     assert apex.check_device_error() == 0
 
 
+def by_waves(apex, lens, Hq, Hkv):  # noqa: F811
+    """The default grid gives whole pairs to single waves (lens: the cached
+    lengths).  The pair cut needs at most one pair per work group, so more pairs
+    than that and a plan by pairs are the waves'."""
+    plan = apex.plan_pairs_host(lens, Hq, Hkv, 512, 256)
+    pairs = int((np.asarray(lens) > 0).sum()) * Hkv
+    return pairs > 512 and plan["active"] == 512 and int(plan["parts"].max()) == 1
+
+
 # (lens, Hq, Hkv): pairs around one per work group (512) and one per wave
-# (2048), one and eight requests per lane, blocks up to the largest (32), block
-# edges, empty requests and requests whose only token is the current one
+# (2048), each group size, one, four and eight requests per lane, blocks up to
+# the largest (32), block edges, empty requests and requests whose only token is
+# the current one
 SHORT = [
     ("513_pairs", [1, 16, 17] * 57, 12, 3),
-    ("520_pairs_65", [100, 7, 1] * 21 + [9, 0], 8, 8),
+    ("536_pairs_g1", [20, 7, 1] * 22 + [9, 0], 8, 8),
     ("2048_pairs", [33, 5, 60, 128] * 64, 16, 8),
     ("2056_pairs", [20, 1, 16, 30] * 64 + [48], 64, 8),
+    ("2112_pairs_g1", [33, 5, 60, 20] * 16 + [0], 33, 33),
+    ("4100_pairs_g1", [19, 64, 2, 48] * 102 + [7, 31], 10, 10),
     ("ragged_32_blocks", [int(x) for x in np.random.default_rng(3).integers(0, 513, size=300)], 32, 32),
     ("512_requests", [int(x) for x in np.random.default_rng(4).integers(0, 90, size=512)], 32, 16),
 ]
@@ -123,8 +135,7 @@ SHORT = [
 @pytest.mark.parametrize("name,lens,Hq,Hkv", SHORT, ids=[c[0] for c in SHORT])
 def test_short_pairs_per_wave(torch_cuda, apex, oracle_mod, name, lens, Hq, Hkv):  # noqa: F811
     torch = torch_cuda
-    plan = apex.plan_pairs_host(lens, Hq, Hkv, 512, 256)
-    assert plan["active"] == 512 and plan["parts"].max() == 1
+    assert by_waves(apex, lens, Hq, Hkv)
     case = W.make_host_case(lens, Hq, Hkv, seed=len(lens) + Hq, poison=True)
     ref, lse_ref = oracle_mod.decode_attention_f64(case.q, case.k_cache, case.v_cache, case.block_table,
                                                    case.context_lens, case.scale, return_lse=True)
@@ -142,12 +153,14 @@ def test_short_pairs_per_wave(torch_cuda, apex, oracle_mod, name, lens, Hq, Hkv)
     assert np.all(np.abs(got[~empty].astype(np.float64) - ref[~empty]) <= fp16_ulp(ref[~empty]) + FP32_ALLOWANCE)
 
 
-@pytest.mark.parametrize("name,lens,Hq,Hkv", SHORT[:4], ids=[c[0] for c in SHORT[:4]])
+@pytest.mark.parametrize("name,lens,Hq,Hkv", SHORT[:6], ids=[c[0] for c in SHORT[:6]])
 @pytest.mark.parametrize("check", [False, True])
 def test_short_pairs_with_the_fused_append(torch_cuda, apex, oracle_mod, name, lens, Hq, Hkv, check):  # noqa: F811
     """The fused append equals the append followed by the plain call: outputs
-    to the bar, caches bit for bit (the current slots hold NaN before)."""
+    and log-sum-exp to the bar, caches bit for bit (the current slots hold NaN
+    before)."""
     torch = torch_cuda
+    assert by_waves(apex, lens, Hq, Hkv)
     lens = [L + 1 if L else 0 for L in lens]
     case = W.make_host_case(lens, Hq, Hkv, seed=7 + len(lens), poison=True)
     rng = np.random.default_rng(8)
@@ -159,10 +172,17 @@ def test_short_pairs_with_the_fused_append(torch_cuda, apex, oracle_mod, name, l
             blk, pos = case.block_table[b, (L - 1) // 16], (L - 1) % 16
             k[blk, :, pos], v[blk, :, pos] = kn[b], vn[b]
             k0[blk, :, pos] = v0[blk, :, pos] = np.nan
-    ref = oracle_mod.decode_attention_f64(case.q, k, v, case.block_table, case.context_lens, case.scale)
+    ref, lse_ref = oracle_mod.decode_attention_f64(case.q, k, v, case.block_table, case.context_lens, case.scale,
+                                                   return_lse=True)
     dev = [torch.from_numpy(x).cuda() for x in (case.q, k0, v0, case.block_table, case.context_lens, kn, vn)]
-    got = apex.decode_attention_ex(*dev[:5], case.scale, k_new=dev[5], v_new=dev[6], check_inputs=check)
-    assert_parity(got.cpu().numpy(), ref, f"{name} fused, check={check}")
+    lse = torch.zeros((len(lens), Hq), dtype=torch.float32, device="cuda")
+    got = apex.decode_attention_ex(*dev[:5], case.scale, k_new=dev[5], v_new=dev[6], check_inputs=check, lse_out=lse)
+    got, lse, some = got.cpu().numpy(), lse.cpu().numpy(), np.asarray(lens) > 0
+    assert_parity(got, ref, f"{name} fused, check={check}")
+    # every output is an fp16 neighbour of the exact value, up to fp32 rounding
+    assert np.all(np.abs(got[some].astype(np.float64) - ref[some]) <= fp16_ulp(ref[some]) + FP32_ALLOWANCE)
+    # fp32 sums of at most 513 weights and one logarithm
+    assert np.abs(lse[some] - lse_ref[some]).max() <= 1e-5 and np.all(np.isneginf(lse[~some]))
     assert np.array_equal(dev[1].cpu().numpy().view(np.uint16), k.view(np.uint16))
     assert np.array_equal(dev[2].cpu().numpy().view(np.uint16), v.view(np.uint16))
     assert not check or apex.check_device_error() == 0
@@ -173,7 +193,7 @@ def test_short_pairs_skip_block_ids_outside_the_pool(torch_cuda, apex, oracle_mo
     block of a pair, and a pair that has no other."""
     lens = [40, 16, 64, 33] * 128
     case = W.make_host_case(lens, 2, 2, seed=11, poison=False)
-    assert apex.plan_pairs_host(lens, 2, 2, 512, 256)["active"] == 512
+    assert by_waves(apex, lens, 2, 2)
     bad = {0: 0, 1: 0, 2: 2, 3: 2, 511: 1, 262: 0}
     keep = case.block_table.copy()
     for b, i in bad.items():
@@ -195,20 +215,27 @@ def test_short_pairs_skip_block_ids_outside_the_pool(torch_cuda, apex, oracle_mo
 
 
 @pytest.mark.parametrize("Hq,Hkv", [(4, 4), (16, 2)])
-def test_short_pairs_keep_infinite_values(torch_cuda, apex, Hq, Hkv):  # noqa: F811
+def test_short_pairs_keep_infinite_values(torch_cuda, apex, oracle_mod, Hq, Hkv):  # noqa: F811
     """An infinite value in the current token's V row (its weight is positive)
-    gives that infinity in its dim, as the cost line does; the other dims stay finite."""
+    gives that infinity in its dim, as the cost line does; the other dims are
+    what they are without it."""
     torch = torch_cuda
     lens = [17, 33, 20, 50] * (1024 // (4 * Hkv))
-    assert apex.plan_pairs_host([L - 1 for L in lens], Hq, Hkv, 512, 256)["active"] == 512
+    assert by_waves(apex, [L - 1 for L in lens], Hq, Hkv)
     case = W.make_host_case(lens, Hq, Hkv, seed=5, poison=False)
     rng = np.random.default_rng(9)
     kn, vn = (rng.standard_normal((len(lens), Hkv, 128)).astype(np.float16) for _ in range(2))
     vn[0, 0, 0], vn[7, -1, 127], vn[-1, 0, 64] = np.inf, -np.inf, np.inf
     want = np.repeat(np.where(np.isinf(vn), vn, np.float16(0)), Hq // Hkv, axis=1)
+    k, v = case.k_cache.copy(), case.v_cache.copy()
+    for b, L in enumerate(lens):
+        blk, pos = case.block_table[b, (L - 1) // 16], (L - 1) % 16
+        k[blk, :, pos], v[blk, :, pos] = kn[b], np.where(np.isinf(vn[b]), np.float16(0), vn[b])
+    ref = oracle_mod.decode_attention_f64(case.q, k, v, case.block_table, case.context_lens, case.scale)
     for kw in ({}, dict(num_workers=512)):   # pairs by waves; an explicit grid is cut on the line
         dev = [torch.from_numpy(x).cuda() for x in (case.q, case.k_cache, case.v_cache, case.block_table,
                                                     case.context_lens, kn, vn)]
         got = apex.decode_attention_ex(*dev[:5], case.scale, k_new=dev[5], v_new=dev[6], **kw).cpu().numpy()
         assert not np.isnan(got).any(), kw
         assert np.array_equal(np.where(np.isinf(got), got, np.float16(0)), want), kw
+        assert_parity(np.where(want == 0, got, ref.astype(np.float16)), ref, f"finite values, {kw}")
