@@ -5,18 +5,21 @@
 // per cache.  A pass of a 256-lane work group covers 256 / (d / 8)
 // consecutive (token, kv-head) rows, so the reads of a wave are contiguous in
 // the new-row buffer and every write is a whole 16-byte-aligned piece of one
-// cache row; a work group makes two passes with all loads in flight before the
-// stores.  The rows are asked for together with their slots, not after them; a
-// padding or out-of-pool slot only drops the store.
+// cache row; a work group makes two passes.  Both rows' slots are asked for
+// first, then the rows, and only those whose slot is in the pool: a padding or
+// out-of-pool token costs its slot and nothing else.
 //
 // A decode step's append (a few hundred rows) is bound by the launch and one
-// chain of instructions and round trips: a division per row in 64 bits and the
-// rows waiting for their slot made it 3.8 us for 32 tokens of 8 kv-heads; with
-// shifts (kPow2: vectors per row, kv-heads and block size are powers of two,
-// else 32-bit divisions where they hold the slot) it takes 2.1.  One, two,
-// four, eight rows per thread: 2.07, 2.11, 2.97, 6.5 us there and 82.6, 82.7,
-// 84.8, 140 us for 54777 tokens.  That call is bound by HBM, reads and writes
-// together: 88.4 -> 82.7 us, 5.43 TB/s.
+// chain of instructions and round trips: divisions in 64 bits and one row after
+// the other made it 3.7 us for 32 tokens of 8 kv-heads (back to back in a
+// graph); with shifts (kPow2: vectors per row, kv-heads and block size are
+// powers of two, else 32-bit divisions where they hold the slot) it takes 2.06.
+// Asking for the rows together with the slots takes 1.98, but then padding is
+// read too, which a bucketed prompt pays for: 54777 tokens, of them no, half,
+// 95 % padding: 69.9, 50.9, 34.1 us that way, 70.9, 36.7, 7.9 this way (the
+// divisions' kernel: 81.3, 37.5, 14.5).  A call without padding is bound by
+// HBM, reads and writes together.  Rows per thread (one, two, four): 70.8, 70.9,
+// 74.7 us there.
 #include <hip/hip_runtime.h>
 
 #include <limits.h>
@@ -60,23 +63,26 @@ __global__ __launch_bounds__(kAppendThreads) void kv_append_kernel(
     const int64_t base = (int64_t)blockIdx.x * s.rows_per_pass * kRows + local_row;
     u32x4 kv[kRows], vv[kRows];
     int64_t slot[kRows];
-    unsigned g[kRows];
+    unsigned t[kRows], g[kRows];
 #pragma unroll
     for (int i = 0; i < kRows; ++i) {
-        slot[i] = -1;
         const int64_t r64 = base + (int64_t)i * s.rows_per_pass;
-        if (r64 >= s.rows) continue;
-        const unsigned r = (unsigned)r64;
-        const unsigned t = kPow2 ? r >> s.head_shift : r / (unsigned)s.Hkv;
-        g[i] = r - t * (unsigned)s.Hkv;
-        slot[i] = slots[t];
-        const int64_t src = (int64_t)t * s.token_vecs + (int64_t)(g[i] * (unsigned)s.row_vecs + c);
+        const unsigned r = (unsigned)(r64 < s.rows ? r64 : s.rows - 1);
+        t[i] = kPow2 ? r >> s.head_shift : r / (unsigned)s.Hkv;
+        g[i] = r - t[i] * (unsigned)s.Hkv;
+        const int64_t at = slots[t[i]];   // every row's slot is in flight before the first is needed
+        slot[i] = r64 < s.rows && at < s.capacity ? at : -1;
+    }
+#pragma unroll
+    for (int i = 0; i < kRows; ++i) {
+        if (slot[i] < 0) continue;
+        const int64_t src = (int64_t)t[i] * s.token_vecs + (int64_t)(g[i] * (unsigned)s.row_vecs + c);
         kv[i] = kStream ? __builtin_nontemporal_load(&k_new[src]) : k_new[src];
         vv[i] = kStream ? __builtin_nontemporal_load(&v_new[src]) : v_new[src];
     }
 #pragma unroll
     for (int i = 0; i < kRows; ++i) {
-        if (slot[i] < 0 || slot[i] >= s.capacity) continue;
+        if (slot[i] < 0) continue;
         int64_t block, pos;
         if (kPow2) {
             block = slot[i] >> s.block_shift;

@@ -41,3 +41,27 @@ def test_large_appends(torch_cuda, apex, T, Hkv, d, bs):  # noqa: F811
         want = torch.full((NB, Hkv, bs, d), 7, dtype=torch.int16, device="cuda")
         want[slots[used] // bs, :, slots[used] % bs] = kv[:, i].view(torch.int16)[used]
         assert torch.equal(caches[i].view(torch.int16), want)
+
+
+def test_padding_costs_its_slots_only(torch_cuda, apex):  # noqa: F811
+    """54 000 tokens of which 95 % are padding: their new rows are not read, so
+    the call takes about a ninth of the time without padding (half when every
+    row is read).  The best of several runs of ten calls each."""
+    torch = torch_cuda
+    T, Hkv, d, bs = 54000, 8, 128, 16
+    NB = -(-T // bs)
+    kv = torch.zeros((T, 2, Hkv, d), dtype=torch.float16, device="cuda")
+    caches = [torch.zeros((NB, Hkv, bs, d), dtype=torch.float16, device="cuda") for _ in range(2)]
+    full = torch.arange(T, device="cuda")
+    padded = torch.where(full < T // 20, full, -1)
+    best = {}
+    for name, slots in (("full", full), ("padded", padded)) * 5:
+        ev = [torch.cuda.Event(enable_timing=True) for _ in range(2)]
+        ev[0].record()
+        for _ in range(10):
+            apex.kv_append(kv[:, 0], kv[:, 1], caches[0], caches[1], slots)
+        ev[1].record()
+        torch.cuda.synchronize()
+        best[name] = min(best.get(name, 1e9), ev[0].elapsed_time(ev[1]) * 100)
+    print(f"[append] {T} tokens: {best['full']:.1f} us, 95 % padding {best['padded']:.1f} us", flush=True)
+    assert best["padded"] < 0.3 * best["full"]
