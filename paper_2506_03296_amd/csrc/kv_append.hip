@@ -35,6 +35,7 @@ using apex::fail;
 constexpr int kAppendThreads = 256;
 constexpr int kMaxRowVecs = kAppendThreads;   // d <= 2048
 constexpr int kRows = 2;                      // rows per thread
+constexpr int64_t kMaxGridX = 1 << 23;        // 2^31 threads
 // The cache rows are written non-temporally: the attention that reads them
 // streams past the caches.  The new rows come out of a projection that has
 // just written them, so up to half the 256 MB Infinity Cache they are read
@@ -60,7 +61,8 @@ __global__ __launch_bounds__(kAppendThreads) void kv_append_kernel(
     const unsigned local_row = kPow2 ? threadIdx.x >> s.vec_shift : threadIdx.x / (unsigned)s.row_vecs;
     const unsigned c = threadIdx.x - local_row * (unsigned)s.row_vecs;
     if (local_row >= (unsigned)s.rows_per_pass) return;
-    const int64_t base = (int64_t)blockIdx.x * s.rows_per_pass * kRows + local_row;
+    const int64_t group = (int64_t)blockIdx.y * gridDim.x + blockIdx.x;
+    const int64_t base = group * s.rows_per_pass * kRows + local_row;
     u32x4 kv[kRows], vv[kRows];
     int64_t slot[kRows];
     unsigned t[kRows], g[kRows];
@@ -109,9 +111,13 @@ template <bool kPow2, bool kStream>
 void launch_append(const void* k_new, const void* v_new, void* k_cache, void* v_cache, const int64_t* slots,
                    const AppendShape& s, hipStream_t stream)
 {
+    // a grid dimension holds fewer than 2^32 threads: a longer one wraps without
+    // an error, so more groups than kMaxGridX go into a second dimension (an
+    // even cut; the last row's surplus groups find no rows)
     const int64_t per_group = (int64_t)s.rows_per_pass * kRows;
-    const unsigned groups = (unsigned)((s.rows + per_group - 1) / per_group);
-    kv_append_kernel<kPow2, kStream><<<groups, kAppendThreads, 0, stream>>>(
+    const int64_t groups = (s.rows + per_group - 1) / per_group;
+    const int64_t y = (groups + kMaxGridX - 1) / kMaxGridX, x = (groups + y - 1) / y;
+    kv_append_kernel<kPow2, kStream><<<dim3((unsigned)x, (unsigned)y), kAppendThreads, 0, stream>>>(
         (const u32x4*)k_new, (const u32x4*)v_new, (u32x4*)k_cache, (u32x4*)v_cache, slots, s);
 }
 

@@ -65,3 +65,28 @@ def test_padding_costs_its_slots_only(torch_cuda, apex):  # noqa: F811
         best[name] = min(best.get(name, 1e9), ev[0].elapsed_time(ev[1]) * 100)
     print(f"[append] {T} tokens: {best['full']:.1f} us, 95 % padding {best['padded']:.1f} us", flush=True)
     assert best["padded"] < 0.3 * best["full"]
+
+
+def test_more_work_groups_than_one_grid_dimension_holds(torch_cuda, apex):  # noqa: F811
+    """2^25 + 5 rows of 129 vectors, one row per pass of a work group: more
+    threads than a grid dimension counts to.  Nearly all tokens are padding; the
+    others are the first, the last and those around the cuts of the grid."""
+    torch = torch_cuda
+    torch.cuda.empty_cache()
+    T, d = (1 << 25) + 5, 1032
+    if torch.cuda.mem_get_info()[0] < 80 << 30:
+        pytest.skip("needs 70 GB of free device memory")
+    new = torch.empty((T, 1, d), dtype=torch.float16, device="cuda")     # K and V: one buffer serves both
+    rows = [0, 1, (1 << 23) - 1, 1 << 23, (1 << 24) - 1, 1 << 24, (1 << 24) + 3, (1 << 25) - 1, 1 << 25, T - 1]
+    slots = torch.full((T,), -1, dtype=torch.int64, device="cuda")
+    want = torch.full((1, 1, 16, d), 9, dtype=torch.float16, device="cuda")
+    for i, r in enumerate(rows):
+        new[r] = i + 1
+        slots[r] = 15 - i
+        want[0, 0, 15 - i] = i + 1
+    caches = [torch.full((1, 1, 16, d), 9, dtype=torch.float16, device="cuda") for _ in range(2)]
+    apex.kv_append(new, new, caches[0], caches[1], slots)
+    torch.cuda.synchronize()
+    assert torch.equal(caches[0], want) and torch.equal(caches[1], want)
+    del new, slots
+    torch.cuda.empty_cache()
