@@ -21,6 +21,7 @@ HEADERS = [os.path.join(ROOT, "include", "apex_decode.h"),
            os.path.join(ROOT, "include", "apex_kv_append.h"),
            os.path.join(ROOT, "include", "apex_decode_trace.h"),
            os.path.join(CSRC, "kernels.h"), os.path.join(CSRC, "plan_policy.h"),
+           os.path.join(CSRC, "append_index.h"),
            os.path.join(CSRC, "status.h")]
 
 HIPCC_FLAGS = [

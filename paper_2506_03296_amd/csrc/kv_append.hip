@@ -26,10 +26,12 @@
 #include <stdint.h>
 
 #include "apex_kv_append.h"
+#include "append_index.h"
 #include "status.h"
 
 namespace {
 
+using apex::AppendShape;
 using apex::fail;
 
 constexpr int kAppendThreads = 256;
@@ -44,14 +46,6 @@ constexpr int64_t kMaxGridX = 1 << 23;        // 2^31 threads
 constexpr int64_t kCachedNewBytes = (int64_t)128 << 20;
 
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
-
-// The shape of a call: vectors per row, rows per pass of a work group, and
-// (kPow2 builds) the logarithms of vectors per row, kv-heads and block size.
-struct AppendShape {
-    int rows, Hkv, row_vecs, rows_per_pass, block_size;
-    int vec_shift, head_shift, block_shift;
-    int64_t token_vecs, capacity;
-};
 
 template <bool kPow2, bool kStream>
 __global__ __launch_bounds__(kAppendThreads) void kv_append_kernel(
@@ -78,25 +72,14 @@ __global__ __launch_bounds__(kAppendThreads) void kv_append_kernel(
 #pragma unroll
     for (int i = 0; i < kRows; ++i) {
         if (slot[i] < 0) continue;
-        const int64_t src = (int64_t)t[i] * s.token_vecs + (int64_t)(g[i] * (unsigned)s.row_vecs + c);
+        const int64_t src = apex::append_source(s, t[i], g[i], c);
         kv[i] = kStream ? __builtin_nontemporal_load(&k_new[src]) : k_new[src];
         vv[i] = kStream ? __builtin_nontemporal_load(&v_new[src]) : v_new[src];
     }
 #pragma unroll
     for (int i = 0; i < kRows; ++i) {
         if (slot[i] < 0) continue;
-        int64_t block, pos;
-        if (kPow2) {
-            block = slot[i] >> s.block_shift;
-            pos = slot[i] & (s.block_size - 1);
-        } else if (((uint64_t)slot[i] >> 32) == 0) {
-            block = (unsigned)slot[i] / (unsigned)s.block_size;
-            pos = slot[i] - block * s.block_size;
-        } else {
-            block = slot[i] / s.block_size;
-            pos = slot[i] - block * s.block_size;
-        }
-        const int64_t dst = ((block * s.Hkv + g[i]) * s.block_size + pos) * s.row_vecs + c;
+        const int64_t dst = apex::append_target<kPow2>(s, slot[i], g[i], c);
         __builtin_nontemporal_store(kv[i], &k_cache[dst]);
         __builtin_nontemporal_store(vv[i], &v_cache[dst]);
     }

@@ -10,7 +10,9 @@
 //     (every non-empty pair's cost positions, then its blocks);
 //   - the strategy selection (Eq. 1-8, Alg. 1-2) on random valid inputs;
 //   - the partition's 32-bit arithmetic (the kernel's path when
-//     V (launched + 1) < 2^32) against its 64-bit form.
+//     V (launched + 1) < 2^32) against its 64-bit form;
+//   - the KV append's row positions against their definition in wide integers,
+//     token rows past 2^32 vectors among them.
 // Usage: driver <cases> <mode: all | threads>; exit status 0 when every
 // check holds.
 #include <immintrin.h>
@@ -24,6 +26,7 @@
 #include <random>
 #include <vector>
 
+#include "append_index.h"
 #include "apex_cpu_attention.h"
 #include "apex_decode.h"
 #include "apex_sched.h"
@@ -214,6 +217,44 @@ void width_case(std::mt19937_64& rng)
     }
 }
 
+// One shape of the KV append, up to the largest a call may have (T Hkv < 2^31,
+// d <= 2048, 63-bit extents): sampled rows lie where the layout says.
+void append_case(std::mt19937_64& rng)
+{
+    auto log_pick = [&](int bits) -> int64_t { return 1 + (int64_t)(rng() & (((uint64_t)1 << (rng() % (bits + 1))) - 1)); };
+    auto exact_log2 = [](int64_t x) -> int { return (x & (x - 1)) == 0 ? __builtin_ctzll((uint64_t)x) : -1; };
+    apex::AppendShape s;
+    memset(&s, 0, sizeof(s));
+    const bool pow2 = rng() % 2;
+    auto shaped = [&](int64_t x) -> int64_t { return pow2 ? (int64_t)1 << (63 - __builtin_clzll((uint64_t)x)) : x; };
+    s.Hkv = (int)shaped(std::min<int64_t>(log_pick(31), INT32_MAX));
+    s.row_vecs = (int)shaped(std::min<int64_t>(log_pick(8), 256));
+    s.block_size = (int)shaped(log_pick(12));
+    const int64_t T = std::max<int64_t>(1, std::min<int64_t>(log_pick(31), INT32_MAX / s.Hkv));
+    s.token_vecs = (int64_t)s.Hkv * s.row_vecs + (rng() % 2 ? 0 : log_pick(8));
+    const int64_t block_vecs = (int64_t)s.Hkv * s.block_size * s.row_vecs;
+    const int64_t blocks = std::max<int64_t>(1, std::min<int64_t>(log_pick(40), INT64_MAX / 32 / block_vecs));
+    s.capacity = blocks * s.block_size;
+    s.vec_shift = exact_log2(s.row_vecs);
+    s.head_shift = exact_log2(s.Hkv);
+    s.block_shift = exact_log2(s.block_size);
+    for (int i = 0; i < 16; ++i) {
+        const bool last = i == 0;
+        const int64_t t = last ? T - 1 : (int64_t)(rng() % (uint64_t)T), g = last ? s.Hkv - 1 : (int64_t)(rng() % s.Hkv);
+        const int64_t c = last ? s.row_vecs - 1 : (int64_t)(rng() % s.row_vecs);
+        const int64_t slot = last ? s.capacity - 1 : (int64_t)(rng() % (uint64_t)s.capacity);
+        const __int128 from = (__int128)t * s.token_vecs + (__int128)g * s.row_vecs + c;
+        check((__int128)apex::append_source(s, (unsigned)t, (unsigned)g, (unsigned)c) == from, "append source", (long)t,
+              (long)g);
+        const __int128 to = (((__int128)(slot / s.block_size) * s.Hkv + g) * s.block_size + slot % s.block_size) *
+                                s.row_vecs + c;
+        check((__int128)apex::append_target<false>(s, slot, (unsigned)g, (unsigned)c) == to, "append target", (long)slot);
+        if (pow2)
+            check((__int128)apex::append_target<true>(s, slot, (unsigned)g, (unsigned)c) == to, "append target by shifts",
+                  (long)slot);
+    }
+}
+
 // One strategy-selection case on random valid inputs (exercised for
 // undefined behaviour; the decisions are checked against the oracle in
 // tests/test_sched.py).
@@ -258,6 +299,7 @@ int main(int argc, char** argv)
             partition_case(rng);
             sched_case(rng);
             for (int j = 0; j < 20; ++j) width_case(rng);
+            for (int j = 0; j < 20; ++j) append_case(rng);
         }
     }
     printf("%d cases, %d failures\n", cases, g_failures);

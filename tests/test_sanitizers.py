@@ -2,8 +2,8 @@
 
 tests/sanitize/driver.cpp runs seeded random cases through the fp64 oracle,
 the host paged-attention backend (compared with the oracle), the partition's
-host mirror (against an explicit line of positions) and the strategy
-selection.  It is built with g++ twice: with AddressSanitizer +
+host mirror (against an explicit line of positions), the strategy selection and
+the KV append's row positions.  It is built with g++ twice: with AddressSanitizer +
 UndefinedBehaviorSanitizer over all of them, and with ThreadSanitizer over the
 host backend and its thread pool (several thread counts, pool resizes,
 chunked pairs).  Any sanitizer report or failed check fails the test.
