@@ -58,7 +58,18 @@ constexpr int kAttnThreads = 256;
 constexpr int kWaves = kAttnThreads / 64;
 constexpr int kCachedLens = 2048;   // context_lens kept in LDS up to this batch size
 constexpr int kStageFloats = 2048;  // LDS of one wave: its merged state, or the partials it combines
-constexpr int kFewPartials = 4;     // partials that the emitting threads combine on their own
+// Partials that the emitting threads combine on their own, all in flight at
+// once; more are shared by the four waves, which end in another LDS merge.  What
+// a thread takes per partial grows with the group: one element (G = 1 and 2),
+// two (G = 4), four (G = 8).  G = 1, threads against waves: 7 and 8 partials 8.35
+// and 7.96 us against 8.71 and 8.38 (one request of 700 tokens, 32 and 16 heads),
+// 15 and 16 partials 11.10 and 25.94 against 11.39 and 26.24 (3000 and 16000
+// tokens, 16 heads); with the line at 4 the fused call of one request on 32 heads
+// was slower than before the waves shared the combine (2100 tokens: 12.2 us then,
+// 12.7 with the line at 4, 12.3 at 16).  Four requests of 1024 tokens, G = 4, 4-5
+// partials a pair: 9.5 us with the line at 4, 9.8 at 8.
+template <int G>
+constexpr int kFewPartials = G == 1 ? 16 : 4;
 
 struct AttnParams {
     const f16* q;          // [B][Hq][D]
@@ -877,9 +888,7 @@ __device__ inline void fold_sums(const u32x2 (&ml)[C], int n, RowState<N>& r, fl
 }
 
 // Combines up to C partials of a pair at elements [e0, e0 + N) of its rows
-// (all of head h), all in flight at once.  Up to kFewPartials this is faster
-// than combine_wave, which ends in another LDS merge (4 requests of 1024
-// tokens, 4-5 partials a pair: 9.5 us with the line at 4, 9.8 at 8).
+// (all of head h), all in flight at once (C <= kFewPartials).
 template <int G, int N, int C>
 __device__ inline void combine_few(const AttnParams& p, int wf, int nc, int e0, int h, RowState<N>& r)
 {
@@ -1487,12 +1496,17 @@ __global__ __launch_bounds__(kAttnThreads) __attribute__((amdgpu_waves_per_eu(2)
                 r.M = -INFINITY;
                 r.den = 0.f;
                 r.num = 0.f;
-                if (nc <= kFewPartials) {
+                constexpr int few = kFewPartials<G>;
+                if (nc <= few) {
                     if (emits) {
                         if (nc <= 2)
                             combine_few<G, N, 2>(p, wf, nc, tid * N, h, r);
+                        else if (nc <= 4)
+                            combine_few<G, N, 4>(p, wf, nc, tid * N, h, r);
+                        else if (nc <= 8 && few >= 8)
+                            combine_few<G, N, few < 8 ? few : 8>(p, wf, nc, tid * N, h, r);
                         else
-                            combine_few<G, N, kFewPartials>(p, wf, nc, tid * N, h, r);
+                            combine_few<G, N, few>(p, wf, nc, tid * N, h, r);
                         emit(r);
                     }
                 } else {

@@ -53,11 +53,12 @@ def test_partition_forms_agree(torch_cuda, apex, oracle_mod, B, Hq, Hkv):  # noq
 
 
 @pytest.mark.parametrize("G", [1, 2, 4, 8])
-@pytest.mark.parametrize("workers", [2, 3, 4, 5, 15, 16, 17, 33, 130])
+@pytest.mark.parametrize("workers", [2, 3, 4, 5, 8, 9, 15, 16, 17, 33, 130])
 def test_combine_of_a_split_pair(torch_cuda, apex, oracle_mod, G, workers):  # noqa: F811
     """One pair on `workers` work groups (one unit and a bit each): every count
-    around what the emitting threads combine on their own (4) and around what
-    four waves hold in flight at once (8 or 16), several rounds beyond it."""
+    around what the emitting threads combine on their own (4; G = 1: 4, 8 and 16
+    at a time) and around what four waves hold in flight at once (8 or 16),
+    several rounds beyond it."""
     torch = torch_cuda
     L = 16 * workers + 5
     case = W.make_host_case([L], G, 1, seed=workers * 8 + G, poison=True)
