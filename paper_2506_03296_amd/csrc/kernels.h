@@ -255,6 +255,8 @@ constexpr int kStreamingLoad = 2;
 // agent scope): work groups on different XCDs, each with its own L2, see each
 // other's values without any cache flush.
 constexpr int kCoherent = 16;
+// s_waitcnt operand: LDS (and scalar) accesses complete, others left in flight
+constexpr int kWaitLds = 0xc07f;
 
 // Operand layouts of one slab (lane = 16 q + c, q = lane / 16, c = lane % 16):
 //   K: word i of lane (c, q) = token c, dims [32i + 8q, +8)   (A of S^T = K Q^T)
@@ -953,6 +955,10 @@ __device__ inline void combine_wave(const AttnParams& p, int wf, int c0, int c1,
     for (; c0 < c1; c0 += C) {
         const int n = c1 - c0 < C ? c1 - c0 : C;
         const Partials<G> ps(p, wf, c0, n);
+        // the reads of the round before are complete before its rows are
+        // overwritten: what a load writes to LDS is not ordered behind them
+        asm volatile("" ::: "memory");
+        __builtin_amdgcn_s_waitcnt(kWaitLds);
         u32x2 ml[C];
 #pragma unroll
         for (int j = 0; j < C; ++j) {
