@@ -1348,6 +1348,7 @@ __global__ __launch_bounds__(kAttnThreads) __attribute__((amdgpu_waves_per_eu(2)
         // every wave takes whole pairs of its own, launched * kWaves pairs
         // apart: no barrier, no merge, the rows straight from its registers
 #ifdef APEX_TRACE_WORK_GROUPS
+        __syncthreads();   // the row is cleared before the waves count into it
         if (tid == 0) s_trace[1] = trace_clock();
 #endif
         const int wv = uniform(wave);
@@ -1364,9 +1365,9 @@ __global__ __launch_bounds__(kAttnThreads) __attribute__((amdgpu_waves_per_eu(2)
             wave_attend<G, kCheck, kAppend, 1>(p, cs, cs, bt, false, Lp, st, wave, lane, ws, s_new[wv], row, unused);
             emit_wave<G, kCheck, kAppend>(p, ws, bp, cs.g, Lp + 1, lane, s_new[wv], row, bt);
 #ifdef APEX_TRACE_WORK_GROUPS
-            if (tid == 0) {
-                ++s_trace[4];
-                s_trace[6] += cs.n;
+            if (lane == 0) {
+                atomicAdd((unsigned long long*)&s_trace[4], 1ull);
+                atomicAdd((unsigned long long*)&s_trace[6], (unsigned long long)cs.n);
             }
 #endif
         }
@@ -1575,6 +1576,7 @@ __global__ __launch_bounds__(kAttnThreads) __attribute__((amdgpu_waves_per_eu(2)
         }
     }
 #ifdef APEX_TRACE_WORK_GROUPS
+    __syncthreads();   // every wave has counted
     if (p.trace && tid == 0 && w < p.trace_groups) {
         uint64_t* t = p.trace + w * kTraceWords;
         t[0] = s_trace[0];

@@ -1,7 +1,8 @@
 """The work-group trace build (libapex_decode_trace.so): the same outputs as
 the product library, bit for bit, and a consistent timeline -- every active
-work group's prologue, first tiles and end in order, and the units of all
-work groups adding up to the call's."""
+work group's prologue, first tiles and end in order, the units of all work
+groups adding up to the call's, and each one's segments and units those of the
+partition that the host mirrors describe."""
 import ctypes
 
 import numpy as np
@@ -60,3 +61,79 @@ def test_trace_build_matches_the_product_and_records_a_timeline(torch_cuda):
     for workers in (0, 5):
         a, b = outs[("product", workers)], outs[("trace", workers)]
         assert torch.equal(a.view(torch.int16), b.view(torch.int16)), workers
+
+
+def traced_rows(torch, lens, Hq, Hkv, append=False):
+    """Rows (uint64 words as int64 [W][8]) of one default-grid call of the trace
+    build, W the launched work groups."""
+    import paper_2506_03296_amd as A
+    from paper_2506_03296_amd import wg_trace
+    product, lib = A.load_library(), wg_trace.load_trace_library()
+    case = W.make_host_case(lens, Hq, Hkv, seed=len(lens), poison=False)
+    t = [torch.from_numpy(x).to("cuda") for x in (case.q, case.k_cache, case.v_cache, case.block_table,
+                                                  case.context_lens)]
+    kw = {}
+    if append:
+        kw = {n: torch.randn((len(lens), Hkv, 128), device="cuda").half() for n in ("k_new", "v_new")}
+    buf = torch.zeros((4096, wg_trace.WORDS), dtype=torch.int64, device="cuda")
+    try:
+        A._LIB = lib
+        assert lib.apex_decode_trace_buffer(ctypes.c_void_p(buf.data_ptr()), 4096) == 0
+        A.decode_attention_ex(*t, case.scale, **kw)
+        torch.cuda.synchronize()
+        assert lib.apex_decode_trace_buffer(None, 0) == 0
+    finally:
+        A._LIB = product
+    rows = buf.cpu().numpy()
+    return rows[rows[:, 3] > 0]
+
+
+def assert_as_planned(rows, lens, Hq, Hkv):
+    """The work groups' segments, split segments and units are those of the
+    partition that the host mirrors give for the cached lengths `lens`; returns
+    which of the three it was."""
+    import paper_2506_03296_amd as A
+    nb = np.array([-(-L // 16) if L > 0 else 0 for L in lens])
+    pairs = np.repeat(nb[nb > 0], Hkv)
+    p, n = A.plan_pairs_host(lens, Hq, Hkv, 512, 256), len(rows)
+    seg, split, units = rows[:, 4], rows[:, 5], rows[:, 6]
+    assert n == 512 and int(units.sum()) == int(pairs.sum())
+    if p["active"] == 0:
+        line = A.plan_host(lens, Hkv, 512, cus=256)
+        assert int(split.sum()) == line["partials"] and not np.any(seg[line["active"]:])
+        assert int(seg.sum()) == int(line["contributors"].sum())
+        return "line"
+    if len(pairs) > 512:
+        # work group w's four waves: pairs w, w + 512, w + 1024, ...
+        assert np.array_equal(seg, np.bincount(np.arange(len(pairs)) % 512, minlength=512)) and not split.any()
+        assert np.array_equal(units, np.bincount(np.arange(len(pairs)) % 512, weights=pairs, minlength=512))
+        return "waves"
+    # one part of one pair per work group, in order
+    want = [min(T, b - k * T) for b, T in zip(nb, p["part_units"]) if b for _ in range(Hkv) for k in range(-(-b // T))]
+    cut = [-(-b // T) > 1 for b, T in zip(nb, p["part_units"]) if b for _ in range(Hkv) for k in range(-(-b // T))]
+    assert len(want) == p["active"] and np.array_equal(units[:len(want)], want) and not units[len(want):].any()
+    assert np.array_equal(seg, units > 0) and np.array_equal(split[:len(want)], cut)
+    return "cut"
+
+
+# (lens, Hq, Hkv, partition): pairs around one per work group (512) and one per
+# wave (2048), one to eight requests per lane, requests around the most that the
+# partitions by pairs take (256 and 512), block edges, empty requests
+PARTITIONS = [
+    ("cut_whole_and_split", [1, 255, 256, 257, 300, 0, 513], 8, 2, "cut"),
+    ("cut_512_pairs", [100, 7] * 32, 8, 8, "cut"),
+    ("cut_256_requests", [20, 3, 33, 16] * 64, 4, 1, "cut"),
+    ("line_257_requests", [20, 3, 33, 16] * 64 + [5], 4, 1, "line"),
+    ("line_longest_33", [513] + [500] * 31, 32, 16, "line"),
+    ("line_large", [2100] * 16, 32, 8, "line"),
+    ("waves_513_pairs", [1, 16, 17] * 57, 12, 3, "waves"),
+    ("waves_2048_pairs", [33, 5, 60, 128] * 64, 16, 8, "waves"),
+    ("waves_2112_pairs_g1", [33, 5, 60, 20] * 16 + [0], 33, 33, "waves"),
+    ("waves_512_requests", [int(x) for x in np.random.default_rng(4).integers(0, 90, size=512)], 32, 16, "waves"),
+    ("line_513_requests", [int(x) for x in np.random.default_rng(4).integers(1, 90, size=513)], 32, 16, "line"),
+]
+
+
+@pytest.mark.parametrize("name,lens,Hq,Hkv,way", PARTITIONS, ids=[c[0] for c in PARTITIONS])
+def test_work_groups_take_what_the_host_mirrors_say(torch_cuda, name, lens, Hq, Hkv, way):
+    assert assert_as_planned(traced_rows(torch_cuda, lens, Hq, Hkv), lens, Hq, Hkv) == way
