@@ -1345,14 +1345,20 @@ __global__ __launch_bounds__(kAttnThreads) __attribute__((amdgpu_waves_per_eu(2)
     }
 
     if (short_pairs > 0) {
-        // every wave takes whole pairs of its own, launched * kWaves pairs
-        // apart: no barrier, no merge, the rows straight from its registers
+        // every wave takes whole pairs of its own: no barrier, no merge, the rows
+        // straight from its registers.  The k-th run of `launched` pairs goes to
+        // wave k mod 4 of the work groups, shifted by kPairSkew groups a wave; the
+        // last one, unless whole, to the groups that start first
 #ifdef APEX_TRACE_WORK_GROUPS
         __syncthreads();   // the row is cleared before the waves count into it
         if (tid == 0) s_trace[1] = trace_clock();
 #endif
         const int wv = uniform(wave);
-        for (int i = (int)w + wv * p.launched; i < short_pairs; i += p.launched * kWaves) {
+        const int skew = p.launched > kWaves * kPairSkew ? wv * kPairSkew : 0;
+        for (int first = wv * p.launched; first < short_pairs; first += kWaves * p.launched) {
+            const int from = first + p.launched <= short_pairs ? skew : 0;
+            const int i = first + ((int)w + from < p.launched ? (int)w + from : (int)w + from - p.launched);
+            if (i >= short_pairs) break;
             const int k = uniform((int)((unsigned)i / (unsigned)p.Hkv));
             const int bp = uniform(s_order[k]), Lp = uniform(s_lens[bp]);
             const int32_t* row = bt + (size_t)bp * (size_t)stride;

@@ -177,6 +177,19 @@ __host__ __device__ inline uint32_t pair_part_units(uint32_t nb, uint32_t floor_
 // 200-256 on the line (20.9 us, 27.2 by waves).  Past 32 blocks the streaming
 // hides the line's cost and whole pairs only balance worse (2048 pairs of
 // 512-2048 tokens 204.6 on the line, 220.6 by waves).
+//
+// Which wave takes which pair: pairs follow each other request by request, and
+// the work groups XCD by XCD and CU by CU, both in powers of two.  With pair i on
+// work group i mod launched in every run, a batch with a long request in every
+// second, fourth or eighth place put all its long pairs on a part of the CUs (or
+// XCDs).  So wave k's whole runs start k kPairSkew groups further on: its
+// multiples by 0 to 3 lie about evenly in any 8, 16, ... 256 places.  120 requests,
+// one of 476 tokens to seven of 18, 32 heads: 111 -> 64 us (line 60); 136, one of
+// 403 to seven of 77, 16 heads: 61.6 -> 36.4 (line 40.0).  Batches without a
+// period are 1 % slower on average (273 of them, 0.94 to 1.15), which is their
+// luck with the other order.
+constexpr int kPairSkew = 77;
+
 constexpr int kShortRequests = 512;   // the kernel's in-register partition, eight requests per lane
 constexpr uint32_t kShortPairUnits = 32;
 

@@ -104,9 +104,12 @@ def assert_as_planned(rows, lens, Hq, Hkv):
         assert int(seg.sum()) == int(line["contributors"].sum())
         return "line"
     if len(pairs) > 512:
-        # work group w's four waves: pairs w, w + 512, w + 1024, ...
-        assert np.array_equal(seg, np.bincount(np.arange(len(pairs)) % 512, minlength=512)) and not split.any()
-        assert np.array_equal(units, np.bincount(np.arange(len(pairs)) % 512, weights=pairs, minlength=512))
+        # run r of 512 pairs goes to the groups' wave r mod 4, a whole one shifted
+        # by 77 groups a wave
+        group = [(i - (77 * (i // 512 % 4) if (i // 512 + 1) * 512 <= len(pairs) else 0)) % 512
+                 for i in range(len(pairs))]
+        assert np.array_equal(seg, np.bincount(group, minlength=512)) and not split.any()
+        assert np.array_equal(units, np.bincount(group, weights=pairs, minlength=512))
         return "waves"
     # one part of one pair per work group, in order
     want = [min(T, b - k * T) for b, T in zip(nb, p["part_units"]) if b for _ in range(Hkv) for k in range(-(-b // T))]
@@ -129,6 +132,7 @@ PARTITIONS = [
     ("waves_513_pairs", [1, 16, 17] * 57, 12, 3, "waves"),
     ("waves_2048_pairs", [33, 5, 60, 128] * 64, 16, 8, "waves"),
     ("waves_2112_pairs_g1", [33, 5, 60, 20] * 16 + [0], 33, 33, "waves"),
+    ("waves_period_8", [476] + [18] * 7 + ([300] + [20] * 7) * 10, 32, 32, "waves"),
     ("waves_512_requests", [int(x) for x in np.random.default_rng(4).integers(0, 90, size=512)], 32, 16, "waves"),
     ("line_513_requests", [int(x) for x in np.random.default_rng(4).integers(1, 90, size=513)], 32, 16, "line"),
 ]
