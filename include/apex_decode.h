@@ -226,11 +226,14 @@ int apex_decode_plan_host(const int32_t* context_lens, int B, int Hkv, int block
  * Host mirror of the two partitions by pairs, which the default grid uses
  * instead of the line of apex_decode_plan_host for small batches and for many
  * short pairs.
+ * Both mirrors take the lengths that the work groups attend: for a call with
+ * the fused append context_lens[b] - 1 of a non-empty request (the current
+ * token is not in the caches), and with the input check at most the table row.
  * Pair cut: every (request, kv-head) pair is cut into equal parts (the last may
  * be shorter), one work group each, in (request, kv-head, part) order.  It
  * applies to at most 256 requests whose pairs fit the work groups (`cus` of
  * them up to one pair per CU, else `launched_workers`) in parts of at most 32
- * units (a pair of more than 2304 blocks takes longer parts).
+ * units (a pair of 2432 blocks or more takes longer parts).
  * Short pairs: every pair is taken whole by one wave of a work group.  It
  * applies to at most 512 requests with more pairs than work groups and at most
  * 32 blocks each, where it is estimated to be faster.

@@ -1069,7 +1069,7 @@ __global__ __launch_bounds__(kAttnThreads) __attribute__((amdgpu_waves_per_eu(2)
         WavePlan r;
         int raws[R], Ls[R], nbs[R];
         unsigned cost = 0;
-        int maxb = 0, nonempty = 0;
+        int maxb = 0, maxnb = 0, nonempty = 0;
 #pragma unroll
         for (int i = 0; i < R; ++i) raws[i] = 0;
         if (R > 1 && lane * R + R <= B) {
@@ -1097,6 +1097,7 @@ __global__ __launch_bounds__(kAttnThreads) __attribute__((amdgpu_waves_per_eu(2)
             nbs[i] = (int)(((unsigned)max(Ls[i], 0) + kBlockSize - 1) / kBlockSize);
             const int full = is_cut(raw) ? (int)row_tokens : raw;
             maxb = max(maxb, (int)(((unsigned)max(full, 0) + kBlockSize - 1) / kBlockSize));
+            maxnb = max(maxnb, nbs[i]);
             nonempty += __popcll(__ballot(nbs[i] > 0));
             cost += nbs[i] > 0 ? (unsigned)(nbs[i] + K) : 0u;
             if (lane * R < B) s_lens[lane * R + i] = Ls[i];   // (past B: never read, inside the array)
@@ -1105,8 +1106,10 @@ __global__ __launch_bounds__(kAttnThreads) __attribute__((amdgpu_waves_per_eu(2)
         __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
         const unsigned hi = (unsigned)wave_incl_sum((int)cost), lo = hi - cost;
         const unsigned total = (unsigned)lane_value((int)hi, 63);
-        const int longest = lane_value(wave_incl_max(maxb), 63);
-        r.stride = p.bt_stride > 0 ? p.bt_stride : longest;
+        // the tight table follows the full lengths, the rules below the cached
+        // ones: with the fused append a request may have a block fewer of them
+        const int longest = lane_value(wave_incl_max(append ? maxnb : maxb), 63);
+        r.stride = p.bt_stride > 0 ? p.bt_stride : append ? lane_value(wave_incl_max(maxb), 63) : longest;
         nonempty = uniform(nonempty);
         r.all_nonempty = nonempty == B;
         const uint64_t V64 = (uint64_t)total * (unsigned)p.Hkv;

@@ -141,3 +141,21 @@ PARTITIONS = [
 @pytest.mark.parametrize("name,lens,Hq,Hkv,way", PARTITIONS, ids=[c[0] for c in PARTITIONS])
 def test_work_groups_take_what_the_host_mirrors_say(torch_cuda, name, lens, Hq, Hkv, way):
     assert assert_as_planned(traced_rows(torch_cuda, lens, Hq, Hkv), lens, Hq, Hkv) == way
+
+
+# cached lengths (the fused call's are one longer) whose longest request ends on
+# a block edge: the current token opens a block that no work group attends
+FUSED = [
+    ("cut_longest_32", [512] * 3 + [17] * 29, 32, 16, "cut"),
+    ("cut_longest_16", [256] * 8 + [40] * 8, 8, 8, "cut"),
+    ("waves_longest_32", [512, 16, 16, 16] * 64, 8, 8, "waves"),
+    ("waves_longest_16_g2", [256, 31, 0, 15] * 100, 32, 16, "waves"),
+    ("waves_longest_1", [16, 3, 9, 1] * 128, 8, 8, "waves"),
+    ("line_longest_33", [528] + [500] * 31, 32, 16, "line"),
+]
+
+
+@pytest.mark.parametrize("name,lens,Hq,Hkv,way", FUSED, ids=[c[0] for c in FUSED])
+def test_the_fused_append_is_partitioned_by_its_cached_lengths(torch_cuda, name, lens, Hq, Hkv, way):
+    rows = traced_rows(torch_cuda, [L + 1 if L else 0 for L in lens], Hq, Hkv, append=True)
+    assert assert_as_planned(rows, lens, Hq, Hkv) == way
