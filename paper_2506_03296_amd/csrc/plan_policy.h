@@ -173,10 +173,19 @@ __host__ __device__ inline uint32_t pair_part_units(uint32_t nb, uint32_t floor_
 // and 1.2 us a block for the longest, all waves at once, no barrier, no merge.
 // Kernel time, line -> waves: 2048 pairs of 20-60 tokens 21.2 -> 11.5 us, 2400
 // of 16-48 22.6 -> 13.2, 1280 of 16-130 (G = 8) 21.9 -> 13.2, 2048 of 200-256
-// 46.3 -> 38.7.  The rule compares the two estimates; it keeps 640 pairs of
-// 200-256 on the line (20.9 us, 27.2 by waves).  Past 32 blocks the streaming
-// hides the line's cost and whole pairs only balance worse (2048 pairs of
-// 512-2048 tokens 204.6 on the line, 220.6 by waves).
+// 46.3 -> 38.7.  The rule compares the two estimates, which place the line up to
+// one pair per wave (2048 on 256 CUs): it keeps 640 pairs of 200-256 on the line
+// (20.9 us, 27.2 by waves).  They know neither the bytes nor a second round, in
+// which a wave may get two of the longest and end alone.  Up to 24 blocks, and
+// past two rounds, the waves still win.  Above, in the second round, they do where
+// most pairs are short or all are alike, else the line balances better (over 570
+// batches of 17 to 32 blocks, periodic ones among them, the rule's choice takes
+// 0.80 of the time before there were pairs by waves, at worst 1.06 and 1.015): 2304
+// pairs of 16-512 tokens, 17.3 blocks on average, 62.7 us on the line, 66.1 by
+// waves; 2624 of 310 and 478 in turn, 25: 89.4, 97.5; but 2304 of 128, every
+// sixteenth of 512, 9.5: 46.0, 37.3; 4112 of 512: 175.1, 170.4.  Past 32 blocks the
+// streaming hides the line's cost and whole pairs only balance worse (2048 pairs
+// of 512-2048 tokens 204.6 on the line, 220.6 by waves).
 //
 // Which wave takes which pair: pairs follow each other request by request, and
 // the work groups XCD by XCD and CU by CU, both in powers of two.  With pair i on
@@ -192,11 +201,17 @@ constexpr int kPairSkew = 77;
 
 constexpr int kShortRequests = 512;   // the kernel's in-register partition, eight requests per lane
 constexpr uint32_t kShortPairUnits = 32;
+constexpr uint32_t kLaterRoundUnits = 24;
+constexpr uint32_t kMostlyShortUnits = 12;
 
 __host__ __device__ inline bool waves_take_pairs(uint32_t units, uint32_t pairs, uint32_t longest, uint32_t launched)
 {
-    return pairs > launched && longest <= kShortPairUnits &&
-           (30 + 12 * longest) * (uint64_t)launched <= 70 * (uint64_t)pairs + 5 * (uint64_t)units;
+    if (pairs <= launched || longest > kShortPairUnits ||
+        (30 + 12 * longest) * (uint64_t)launched > 70 * (uint64_t)pairs + 5 * (uint64_t)units)
+        return false;
+    const uint32_t waves = 4 * launched;
+    return pairs <= waves || pairs > 2 * waves || longest <= kLaterRoundUnits ||
+           units <= (uint64_t)kMostlyShortUnits * pairs || 8 * (uint64_t)units > 7 * (uint64_t)longest * pairs;
 }
 
 }  // namespace apex

@@ -23,7 +23,9 @@ def test_parts_cover_every_pair_and_fit_the_work_groups(seed):
         groups = min(cus, launched) if pairs <= cus else launched
         fits = cus > 0 and B <= 256 and 0 < pairs <= groups and (longest <= 32 or units <= 32 * (groups - pairs))
         short = (cus > 0 and not fits and B <= 512 and pairs > launched and longest <= 32
-                 and (30 + 12 * longest) * launched <= 70 * pairs + 5 * units)
+                 and (30 + 12 * longest) * launched <= 70 * pairs + 5 * units
+                 and (pairs <= 4 * launched or pairs > 8 * launched or longest <= 24 or units <= 12 * pairs
+                      or 8 * units > 7 * longest * pairs))
         assert (p["active"] > 0) == (fits or short)
         if short:
             whole += 1
@@ -42,6 +44,31 @@ def test_parts_cover_every_pair_and_fit_the_work_groups(seed):
         assert np.all(parts[used] * T[used] >= blocks[used])           # nothing left over
         assert np.all(parts[blocks <= 16] <= 1)
     assert applied > 20 and whole > 5
+
+
+# Batches measured on the line and by waves (us, line / waves, on 256 CUs and 512
+# work groups): the partition that was faster.  (lens, Hkv, by waves)
+MEASURED = [
+    ([20 + 4 * (i % 11) for i in range(256)], 8, True),            # 21.2 / 11.5
+    ([16 + i % 33 for i in range(300)], 8, True),                  # 22.6 / 13.2
+    ([200 + 4 * (i % 15) for i in range(256)], 8, True),           # 46.3 / 38.7
+    ([200 + 4 * (i % 15) for i in range(80)], 8, False),           # 20.9 / 27.2
+    ([277 + 59 * (i % 2) for i in range(286)], 8, True),           # 72.6 / 65.1
+    ([16 + 31 * i % 497 for i in range(144)], 16, False),          # 62.7 / 66.1
+    ([16 + 31 * i % 497 for i in range(188)], 16, False),          # 74.6 / 78.4
+    ([310 + 168 * (i % 2) for i in range(82)], 32, False),         # 89.4 / 97.5
+    ([34 + 432 * (i % 2) for i in range(262)], 8, False),          # 57.0 / 60.4
+    ([128 + 384 * (i % 16 == 0) for i in range(144)], 16, True),   # 46.0 / 37.3
+    ([512] * 257, 16, True),                                       # 175.1 / 170.4
+    ([1] * 176 + [512] * 12, 16, True),                            # 34.3 / 24.4
+    ([16 + 31 * i % 497 for i in range(388)], 16, True),           # 162.4 / 153.8
+]
+
+
+@pytest.mark.parametrize("lens,Hkv,waves", MEASURED)
+def test_measured_batches_take_the_faster_partition(lens, Hkv, waves):
+    p = A.plan_pairs_host(lens, 4 * Hkv, Hkv, 512, 256)
+    assert len(lens) * Hkv > 512 and p["active"] == (512 if waves else 0)
 
 
 def test_bad_arguments_are_refused():
