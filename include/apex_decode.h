@@ -232,11 +232,12 @@ int apex_decode_plan_host(const int32_t* context_lens, int B, int Hkv, int block
  * Pair cut: every (request, kv-head) pair is cut into equal parts (the last may
  * be shorter), one work group each, in (request, kv-head, part) order.  It
  * applies to at most 256 requests whose pairs fit the work groups (`cus` of
- * them up to one pair per CU, else `launched_workers`) in parts of at most 32
- * units (a pair of 2432 blocks or more takes longer parts).
+ * them up to one pair per CU, else `launched_workers`) in parts of at most 24
+ * units (a pair of 1408 blocks or more takes longer parts), or do not but have
+ * at most 32 units each and stay whole.
  * Short pairs: every pair is taken whole by one wave of a work group.  It
  * applies to at most 512 requests with more pairs than work groups and at most
- * 32 blocks each, where it is estimated to be faster.
+ * 32 blocks each, where it is faster by measured rules.
  * Outputs (any may be NULL): parts_out[B] and part_units_out[B] = parts of each
  * of the request's pairs and units per part (0 for an empty request),
  * *active_out = work groups that get units, 0 when neither applies (then

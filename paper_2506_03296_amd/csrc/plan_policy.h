@@ -132,14 +132,19 @@ __host__ __device__ inline int64_t partial_slot(int64_t w, int64_t wf)
 // parts of at most kPairCutMaxPart units, a work group takes one part of one
 // pair instead.  Kernel time, line -> parts: MHA of 17-511 tokens 10.3 -> 8.0
 // us, 8 pairs of 300 tokens 10.8 -> 7.2, 512 pairs of 20-200 tokens 13.5 ->
-// 10.8; with longer parts the uneven last parts cost what the combine saves,
-// and batches outside the rule tie within 0.5 % on the line.  Pairs of up to
-// kWholePairUnits stay whole: up to four blocks per wave cost less than a
-// combine.  The part grows with the pair (pair_part_units), since a pair's last
+// 10.8.  With longer parts the uneven last ones cost what the combine saves: of
+// 300 batches those with 12 to 24 units per free work group take 0.94 to 0.98 of
+// the line's time on average in parts, with 24 to 26 0.98, with 26 to 30 1.01 to
+// 1.03 and up to 1.14 (270 pairs of 116 and 676 tokens in turn, parts of 29: 21.0
+// us, 18.8 on the line).  Pairs of up to kWholePairUnits stay whole: up to four
+// blocks per wave cost less than a combine; so do pairs of up to kWholeAloneUnits
+// where the parts do not fit (20 such batches: 0.98 of their time in parts of 24
+// to 32 units, never above).  The part grows with the pair (pair_part_units), since a pair's last
 // work group reads all its parts' partials, sooner for G = 8, whose partials
 // are the largest.
-constexpr uint32_t kPairCutMaxPart = 32;
+constexpr uint32_t kPairCutMaxPart = 24;
 constexpr uint32_t kWholePairUnits = 16;
+constexpr uint32_t kWholeAloneUnits = 32;
 
 constexpr int kPairCutRequests = 256;   // the kernel's in-register partition, four requests per lane
 
@@ -152,7 +157,7 @@ __host__ __device__ inline uint32_t pair_cut_floor(uint32_t units, uint32_t pair
     const uint32_t groups = pairs <= cus ? (cus < launched ? cus : launched) : launched;
     if (pairs == 0 || pairs > groups) return 0;
     const uint32_t room = groups - pairs;
-    if (units > room * kPairCutMaxPart) return longest <= kPairCutMaxPart ? longest : 0;
+    if (units > room * kPairCutMaxPart) return longest <= kWholeAloneUnits ? longest : 0;
     if (longest <= kWholePairUnits) return longest;
     return (units + room - 1) / room;
 }

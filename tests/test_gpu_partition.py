@@ -73,7 +73,7 @@ def test_combine_of_a_split_pair(torch_cuda, apex, oracle_mod, G, workers):  # n
 
 
 # (lens, Hq, Hkv, pair cut applies): a pair's blocks around what stays whole
-# (16) and around the largest part (32), pairs around one per CU (256) and one
+# (16; 32 where parts do not fit), parts around the largest (24), pairs around one per CU (256) and one
 # per work group (512), requests in one and in four per lane, long pairs
 PAIR_CUTS = [
     ("whole_and_cut", [1, 255, 256, 257, 300, 0, 513], 8, 2, True),
@@ -85,9 +85,11 @@ PAIR_CUTS = [
     ("512_pairs", [100, 7] * 32, 8, 8, True),
     ("520_pairs", [300, 7] * 32 + [9], 8, 8, False),
     ("100_requests", list(range(1, 401, 4)), 16, 2, True),
-    ("65_heads", [700, 40], 65, 65, True),
+    ("65_heads", [650, 40], 65, 65, True),
     ("long_pair", [60000], 8, 1, True),
     ("two_long_g1", [40000, 333], 2, 2, True),
+    ("parts_of_24", [5760] * 8, 8, 2, True),
+    ("one_unit_more", [5760] * 7 + [5761], 8, 2, False),
     ("large", [2100] * 16, 32, 8, False),
 ]
 

@@ -21,7 +21,7 @@ def test_parts_cover_every_pair_and_fit_the_work_groups(seed):
         blocks = np.where(lens > 0, -(-lens // 16), 0)
         pairs, units, longest = int((blocks > 0).sum()) * Hkv, int(blocks.sum()) * Hkv, int(blocks.max())
         groups = min(cus, launched) if pairs <= cus else launched
-        fits = cus > 0 and B <= 256 and 0 < pairs <= groups and (longest <= 32 or units <= 32 * (groups - pairs))
+        fits = cus > 0 and B <= 256 and 0 < pairs <= groups and (longest <= 32 or units <= 24 * (groups - pairs))
         short = (cus > 0 and not fits and B <= 512 and pairs > launched and longest <= 32
                  and (30 + 12 * longest) * launched <= 70 * pairs + 5 * units
                  and (pairs <= 4 * launched or pairs > 8 * launched or longest <= 24 or units <= 12 * pairs
@@ -69,6 +69,23 @@ MEASURED = [
 def test_measured_batches_take_the_faster_partition(lens, Hkv, waves):
     p = A.plan_pairs_host(lens, 4 * Hkv, Hkv, 512, 256)
     assert len(lens) * Hkv > 512 and p["active"] == (512 if waves else 0)
+
+
+# The same for the line and the pair cut: (lens, Hq, Hkv, parts)
+MEASURED_CUTS = [
+    ([300], 32, 8, True),                                          # 10.8 / 7.2
+    ([2100], 32, 8, True),                                         # 12.6 / 10.1
+    ([20 + 3 * (i % 61) for i in range(64)], 8, 8, True),          # 13.5 / 10.8
+    ([676 - 560 * (i % 2) for i in range(135)], 2, 2, False),      # 18.8 / 21.0
+    ([383 + 130 * (i % 4 == 0) for i in range(17)], 16, 16, False),   # 18.8 / 21.0
+    ([1267] * 8, 8, 8, False),                                     # 12.1 / 13.1
+]
+
+
+@pytest.mark.parametrize("lens,Hq,Hkv,parts", MEASURED_CUTS)
+def test_measured_batches_are_cut_where_parts_are_faster(lens, Hq, Hkv, parts):
+    p = A.plan_pairs_host(lens, Hq, Hkv, 512, 256)
+    assert len(lens) * Hkv <= 512 and (p["active"] > 0) == parts
 
 
 def test_bad_arguments_are_refused():
