@@ -1230,12 +1230,11 @@ __global__ __launch_bounds__(kAttnThreads) __attribute__((amdgpu_waves_per_eu(2)
     int b = plan.b, g = plan.g, blk = plan.blk, L = plan.L;
     int64_t V = plan.V, W = plan.W, v0 = plan.v0, v1 = plan.v1, vf = plan.vf, stride = plan.stride;
 
-    // Larger batches (and partitions past 32 bits): context_lens is read once
-    // by the group, each thread sums the blocks of a contiguous run of
-    // requests (and keeps the lengths in LDS when they fit); wave-level scans
-    // plus one barrier give the prefix sums, the total, the longest request
-    // and the non-empty requests.  Redundant per-wave runs of more than four
-    // requests would cost more than the barriers they save.
+    // More than kShortRequests requests (and partitions past 32 bits):
+    // context_lens is read once by the group, each thread sums the blocks of a
+    // contiguous run of requests (and keeps the lengths in LDS when they fit);
+    // wave-level scans plus one barrier give the prefix sums, the total, the
+    // longest request and the non-empty requests.
     if (!plan.planned) {
     const int seg = (B + kAttnThreads - 1) / kAttnThreads;
     const int r0 = min(B, tid * seg);
