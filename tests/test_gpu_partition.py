@@ -156,7 +156,7 @@ def test_short_pairs_per_wave(torch_cuda, apex, oracle_mod, name, lens, Hq, Hkv)
     assert np.all(np.abs(got[~empty].astype(np.float64) - ref[~empty]) <= fp16_ulp(ref[~empty]) + FP32_ALLOWANCE)
 
 
-@pytest.mark.parametrize("name,lens,Hq,Hkv", SHORT[:6], ids=[c[0] for c in SHORT[:6]])
+@pytest.mark.parametrize("name,lens,Hq,Hkv", SHORT, ids=[c[0] for c in SHORT])
 @pytest.mark.parametrize("check", [False, True])
 def test_short_pairs_with_the_fused_append(torch_cuda, apex, oracle_mod, name, lens, Hq, Hkv, check):  # noqa: F811
     """The fused append equals the append followed by the plain call: outputs
